@@ -13,6 +13,7 @@
 
 #include "../../include/okpz.h"
 #include "db_rows.hpp"
+#include "dt_cells.hpp"
 #include "dt_rows.hpp"
 #include "kernels.hpp"
 #include "philox.hpp"
@@ -261,6 +262,20 @@ inline void step_shape(uint32_t ncell, uint32_t threads, uint32_t &cpt, uint32_t
     } else {
         cpt = ncell / nt;
     }
+}
+
+// Domains the DT step holds in registers (dt_cells.hpp).
+inline bool dt_cells_shape(const okpz_params &p)
+{
+    return p.block_scheme == OKPZ_BLOCK_DT && p.device_layer == OKPZ_DEVICE_DT && p.dom_x == p.dom_y &&
+           (p.dom_x == 128u || p.dom_x == 256u) && p.cell_x == 8u && p.cell_y == 8u;
+}
+
+// Waves per tile of that step.
+inline uint32_t dt_cells_waves(uint32_t threads, uint64_t ntiles, uint32_t cus)
+{
+    if (threads) return threads / 64u;
+    return ntiles < 4ull * cus ? 4u : 1u;
 }
 
 inline StepArgs base_args(const okpz_lattice *lat, const LaneShape &ls, double pd, double qr)

@@ -79,29 +79,55 @@ bool launch_db_rows(uint32_t nt, uint32_t ntiles, hipStream_t st, const StepArgs
     return false;
 }
 
-// The row-paired DT / DTr kernel for square 128- or 256-site domains of
-// 8 x 8-site cells (4 site bits per lane draw, in 16-bit fields with
-// acceptance prefixes, 4-bit fields without), one to four cells per lane.
-template <int SCHEME, bool ACCEPT, int CPT>
-bool launch_dt_rows(uint32_t nt, uint32_t ntiles, hipStream_t st, const StepArgs &a, int &rc)
+// The row-paired DTr kernel for square 128- or 256-site domains of 8 x 8-site
+// cells (4 site bits per lane draw, in 16-bit fields with acceptance
+// prefixes, 4-bit fields without), one to four cells per lane.
+template <bool ACCEPT, int CPT>
+bool launch_dtr_rows(uint32_t nt, uint32_t ntiles, hipStream_t st, const StepArgs &a, int &rc)
 {
-    if constexpr ((SCHEME == kDT || SCHEME == kDTR) && (CPT == 1 || CPT == 2 || CPT == 4)) {
+    if constexpr (CPT == 1 || CPT == 2 || CPT == 4) {
         constexpr uint32_t FL = ACCEPT ? 4u : 2u;
         if (a.Dx != a.Dy || a.log2Cx != 3u || a.log2Cy != 3u || a.s_bits != 4u || a.F_log2 != FL ||
             a.shared_edges)
             return false;
         if (a.Dx == 256u) {
-            rc = launch_instance(&step_dt_rows_kernel<SCHEME, ACCEPT, CPT, 8, 3>, nt, ntiles,
+            rc = launch_instance(&step_dt_rows_kernel<kDTR, ACCEPT, CPT, 8, 3>, nt, ntiles,
                                  4u * rowpair_dt_lds_words<8, 3>(), st, a);
             return true;
         }
         if (a.Dx == 128u) {
-            rc = launch_instance(&step_dt_rows_kernel<SCHEME, ACCEPT, CPT, 7, 3>, nt, ntiles,
+            rc = launch_instance(&step_dt_rows_kernel<kDTR, ACCEPT, CPT, 7, 3>, nt, ntiles,
                                  4u * rowpair_dt_lds_words<7, 3>(), st, a);
             return true;
         }
     }
     return false;
+}
+
+template <int LD, int NW>
+int launch_dt_cells_shape(int mode, uint32_t ntiles, hipStream_t st, const StepArgs &a)
+{
+    constexpr size_t lds = 4u * CellShape<LD, NW>::LDS_WORDS;
+    switch (mode) {
+    case kDeposit: return launch_instance(&step_dt_cells_kernel<kDeposit, LD, NW>, 64u * NW, ntiles, lds, st, a);
+    case kSure: return launch_instance(&step_dt_cells_kernel<kSure, LD, NW>, 64u * NW, ntiles, lds, st, a);
+    default: return launch_instance(&step_dt_cells_kernel<kDraw, LD, NW>, 64u * NW, ntiles, lds, st, a);
+    }
+}
+
+// DT on square 128- or 256-site domains of 8 x 8-site cells: the domain in
+// registers, `nw` waves per tile.
+int launch_dt_cells(uint32_t nw, uint32_t ntiles, hipStream_t st, const StepArgs &a, bool accept)
+{
+    const int mode = accept ? kDraw : a.flip_table == kFlipMin ? kDeposit : kSure;
+    if (a.Dx == 128u)  // two cells a lane at least
+        return nw == 1 ? launch_dt_cells_shape<7, 1>(mode, ntiles, st, a) : launch_dt_cells_shape<7, 2>(mode, ntiles, st, a);
+    switch (nw) {
+    case 1: return launch_dt_cells_shape<8, 1>(mode, ntiles, st, a);
+    case 2: return launch_dt_cells_shape<8, 2>(mode, ntiles, st, a);
+    case 4: return launch_dt_cells_shape<8, 4>(mode, ntiles, st, a);
+    default: return launch_dt_cells_shape<8, 8>(mode, ntiles, st, a);
+    }
 }
 
 // DB runs the row-paired kernel where it applies, else, with at least two
@@ -113,9 +139,9 @@ int launch_step_inst(uint32_t nt, uint32_t ntiles, size_t lds, hipStream_t st, c
     // the dead-border control runs the generic kernel (the only one that
     // masks the tiles' rims and XORs back the words they share)
     if (a.dev_db) return launch_instance(&step_kernel<SCHEME, ACCEPT, CPT>, nt, ntiles, lds, st, a);
-    if constexpr (SCHEME != kDB) {
+    if constexpr (SCHEME == kDTR) {
         int rc = OKPZ_OK;
-        if (launch_dt_rows<SCHEME, ACCEPT, CPT>(nt, ntiles, st, a, rc)) return rc;
+        if (launch_dtr_rows<ACCEPT, CPT>(nt, ntiles, st, a, rc)) return rc;
     }
     if constexpr (SCHEME == kDB && CPT >= 2) {
         int rc = OKPZ_OK;
@@ -155,6 +181,12 @@ int launch_step(okpz_lattice *lat, const StepArgs &a, bool accept)
     const uint32_t ncell = a.ncell;
     const uint32_t span = a.dev_db ? 1u : 2u;  // dead border: every dom_x x dom_y tile in one step
     const uint32_t ntiles = (p.L / (span * p.dom_x)) * (p.L / (span * p.dom_y));
+    if (dt_cells_shape(p)) {
+        const int rc = launch_dt_cells(dt_cells_waves(lat->threads, ntiles, lat->cus), ntiles, lat->stream, a, accept);
+        if (rc != OKPZ_OK) return rc;
+        HIP_TRY(hipGetLastError());
+        return OKPZ_OK;
+    }
     uint32_t cpt, nt;
     step_shape(ncell, lat->threads ? lat->threads : default_threads(ntiles, lat->cus, ncell), cpt, nt);
     if (cpt > 16) return OKPZ_EINVAL;

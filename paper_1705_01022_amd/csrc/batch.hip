@@ -98,30 +98,13 @@ __device__ __forceinline__ u32x4 mcs_origin(const BatchSlot &S, uint64_t m, uint
     return w;
 }
 
-// COLS: every lattice of the launch is DB with lanes x CPT cells per domain
-// and at most 64 cells per row, so the column-mapped sweep serves them all.
-// FL > 0 (with COLS): every lattice also draws 2^FL-bit lane fields, with
-// acceptance draws iff FL = 4 and a whole number of Philox blocks of rounds,
-// so the sweep with the rounds of one block unrolled serves them all.
-//
-// LD > 0 (with COLS and FL > 0): every lattice also has square 2^LD-site
-// domains of 8 x 8-site cells, so the row-paired DB sweep serves them all.
-// LD > 0 with DT or DTr: every lattice has square 128- or 256-site domains of
-// 8 x 8-site cells, and each item runs the row-paired DT sweep for its
-// lattice's domain size and rates.
-//
-// DT and DTr with at most 4 cells per lane: six waves per SIMD (80 VGPRs;
-// the generic sweep spills 40 bytes to scratch for it and ran the
-// 512-realisation batch 5 % faster than the five waves its unconstrained 93
-// VGPRs allow; the row-paired DT sweep fits).  The row-paired DB sweep runs
-// two cells per lane (63 VGPRs): with four, the batch kernel's own state on
-// top of the sweep's needs 117 VGPRs (four waves), or spills at five.
-template <int SCHEME, int CPT, bool COLS, int FL, int LD>
-__global__ void __launch_bounds__(kMaxStepThreads)
-__attribute__((amdgpu_waves_per_eu((SCHEME != kDB && CPT <= 4) || LD > 0 ? 6 : 1)))
-batch_kernel(BatchArgs B)
+// The items of one workgroup, in ticket order, until the queue is empty:
+// sweep(S, A, tile) is the device step of one tile of the lattice of slot S.
+// SHARED: the sweep reads and writes the lattice past the die-private caches by
+// itself, so items need no cache invalidation and no write-back.
+template <bool SHARED, typename Sweep>
+__device__ __forceinline__ void batch_items(const BatchArgs &B, Sweep sweep)
 {
-    extern __shared__ uint32_t smem[];
     // lattice, tile, generation, stop; the neighbourhood to wait for: first
     // column, columns, first row, rows
     __shared__ uint32_t cmd[8];
@@ -212,7 +195,7 @@ batch_kernel(BatchArgs B)
                 const uint64_t any_bad = __ballot(bad);  // every lane of the wave takes part
                 // the earlier steps' words, written by other workgroups, become visible
                 // (the cache invalidation covers the whole workgroup's caches)
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                if (!SHARED) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 if (tid == 0 && any_bad) cmd[3] = 1u;
             }
         }
@@ -238,6 +221,44 @@ batch_kernel(BatchArgs B)
         // the first wave took the agent-scope acquire after its waits, before
         // the barrier above (it invalidates the caches this workgroup reads
         // through, which all its waves share).
+        sweep(S, A, tile);
+        // Publish this tile's words before stamping the tile with generation
+        // g done: every lane waits until its own stores are acknowledged, the
+        // barrier orders them before thread 0, whose agent-scope release store
+        // writes them back for the other dies (once per item, not once per wave).
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (tid == 0)
+            __hip_atomic_store(&B.stamp[my_stamp], g + 1u, SHARED ? __ATOMIC_RELAXED : __ATOMIC_RELEASE,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// COLS: every lattice of the launch is DB with lanes x CPT cells per domain
+// and at most 64 cells per row, so the column-mapped sweep serves them all.
+// FL > 0 (with COLS): every lattice also draws 2^FL-bit lane fields, with
+// acceptance draws iff FL = 4 and a whole number of Philox blocks of rounds,
+// so the sweep with the rounds of one block unrolled serves them all.
+//
+// LD > 0 (with COLS and FL > 0): every lattice also has square 2^LD-site
+// domains of 8 x 8-site cells, so the row-paired DB sweep serves them all.
+// LD > 0 with DTr: every lattice has square 128- or 256-site domains of
+// 8 x 8-site cells, and each item runs the row-paired DTr sweep for its
+// lattice's domain size and rates.
+//
+// DT and DTr with at most 4 cells per lane: six waves per SIMD (80 VGPRs;
+// the generic sweep spills 40 bytes to scratch for it and ran faster than
+// with the five waves its unconstrained 93 VGPRs allow; the row-paired sweep
+// fits).  The row-paired DB sweep runs
+// two cells per lane (63 VGPRs): with four, the batch kernel's own state on
+// top of the sweep's needs 117 VGPRs (four waves), or spills at five.
+template <int SCHEME, int CPT, bool COLS, int FL, int LD>
+__global__ void __launch_bounds__(kMaxStepThreads)
+__attribute__((amdgpu_waves_per_eu((SCHEME != kDB && CPT <= 4) || LD > 0 ? 6 : 1)))
+batch_kernel(BatchArgs B)
+{
+    extern __shared__ uint32_t smem[];
+    batch_items<false>(B, [&](const BatchSlot &S, const StepArgs &A, uint32_t tile) {
         if constexpr (LD > 0 && SCHEME != kDB) {
             if (A.Dx == 256u) {
                 if (S.accept)
@@ -265,14 +286,37 @@ batch_kernel(BatchArgs B)
             else
                 sweep_tile<SCHEME, false, CPT, false>(A, smem, tile);
         }
-        // Publish this tile's words before stamping the tile with generation
-        // g done: every lane waits until its own stores are acknowledged, the
-        // barrier orders them before thread 0, whose agent-scope release store
-        // writes them back for the other dies (once per item, not once per wave).
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (tid == 0) __hip_atomic_store(&B.stamp[my_stamp], g + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    });
+}
+
+// DT members that all hold their domains in registers (dt_cells.hpp), NW waves
+// per workgroup: 128-site domains for one or two, 256-site ones for two or four.
+template <int NW>
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 2 ? 4 : 6)))
+batch_dt_cells_kernel(BatchArgs B)
+{
+    extern __shared__ uint32_t smem[];
+    batch_items<true>(B, [&](const BatchSlot &S, const StepArgs &A, uint32_t tile) {
+        auto run = [&](auto ldc) {
+            constexpr int LD = decltype(ldc)::value;
+            if (S.accept)
+                sweep_dt_cells<kDraw, LD, NW, true>(A, smem, tile);
+            else if (A.flip_table == kFlipMin)
+                sweep_dt_cells<kDeposit, LD, NW, true>(A, smem, tile);
+            else
+                sweep_dt_cells<kSure, LD, NW, true>(A, smem, tile);
+        };
+        if constexpr (NW == 1) {
+            run(std::integral_constant<int, 7>());
+        } else if constexpr (NW == 2) {
+            if (A.Dx == 128u)
+                run(std::integral_constant<int, 7>());
+            else
+                run(std::integral_constant<int, 8>());
+        } else {
+            run(std::integral_constant<int, 8>());
+        }
+    });
 }
 
 __global__ void batch_reset_kernel(uint32_t *stamp, uint32_t n, unsigned long long *ticket)
@@ -497,13 +541,10 @@ const void *batch_fn()
 const void *batch_kernel_for(int scheme, uint32_t cpt, bool cols, int fl, int ld)
 {
     if (scheme != kDB && ld) {
-        switch (cpt * 4 + (uint32_t)(scheme == kDTR ? 1 : 0)) {
-        case 4: return batch_fn<kDT, 1, false, 0, 8>();
-        case 5: return batch_fn<kDTR, 1, false, 0, 8>();
-        case 8: return batch_fn<kDT, 2, false, 0, 8>();
-        case 9: return batch_fn<kDTR, 2, false, 0, 8>();
-        case 16: return batch_fn<kDT, 4, false, 0, 8>();
-        case 17: return batch_fn<kDTR, 4, false, 0, 8>();
+        switch (cpt) {
+        case 1: return batch_fn<kDTR, 1, false, 0, 8>();
+        case 2: return batch_fn<kDTR, 2, false, 0, 8>();
+        case 4: return batch_fn<kDTR, 4, false, 0, 8>();
         default: return nullptr;
         }
     }
@@ -810,10 +851,9 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
         if (ld == 8) lds = 4u * rowpair_lds_words<8, 3>(nt);
         if (ld == 7) lds = 4u * rowpair_lds_words<7, 3>(nt);
     }
-    // DT / DTr with square 128- or 256-site domains of 8 x 8-site cells
-    // throughout, at most four cells per lane: the row-paired DT sweep (the
-    // window alone in LDS)
-    if (b->scheme != kDB && cpt <= 4) {
+    // DTr with square 128- or 256-site domains of 8 x 8-site cells throughout,
+    // at most four cells per lane: the row-paired sweep (the window alone in LDS)
+    if (b->scheme == kDTR && cpt <= 4) {
         bool rows = true, any256 = false;
         for (uint32_t i = 0; i < n && rows; ++i) {
             const StepArgs &a = slots[i].a;
@@ -827,6 +867,28 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
         }
     }
     const void *fn = batch_kernel_for(b->scheme, cpt, cols, fl, ld);
+    // DT members that all hold their domains in registers
+    bool regs = true, any128 = false, any256 = false;
+    for (int32_t s : order) {
+        const okpz_params &prm = b->slots[s]->prm;
+        regs = regs && dt_cells_shape(prm);
+        any128 = any128 || prm.dom_x == 128u;
+        any256 = any256 || prm.dom_x == 256u;
+    }
+    if (regs) {
+        int dev = 0, cus = 0;
+        HIP_TRY(hipGetDevice(&dev));
+        HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        uint32_t nw = any256 ? dt_cells_waves(256u, b->threads, prefix[n], (uint32_t)std::max(cus, 1)) : 1u;
+        if (any128 && any256) nw = 2u;
+        nt = 64u * nw;
+        ld = 8;
+        lds = 4u * (any256 ? (nw == 2u ? CellShape<8, 2>::LDS_WORDS : CellShape<8, 4>::LDS_WORDS)
+                           : CellShape<7, 1>::LDS_WORDS);
+        fn = nw == 1u   ? reinterpret_cast<const void *>(&batch_dt_cells_kernel<1>)
+             : nw == 2u ? reinterpret_cast<const void *>(&batch_dt_cells_kernel<2>)
+                        : reinterpret_cast<const void *>(&batch_dt_cells_kernel<4>);
+    }
     if (!fn) return OKPZ_EINVAL;
     if (lds > 64u * 1024u)
         HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kMaxLds - kStaticLds)));

@@ -1,6 +1,38 @@
 // DT device step with the domain in registers (square domains of 128 or 256
 // sites, 8 x 8-site cells).  Same attempts and random draws as sweep_tile's DT
-// path (Sec. 3 DT at block level, Sec. 3.1 single hit).
+// path (Sec. 3 DT at block level, Sec. 3.1 single hit); the domain's state and
+// the way a round tests it differ:
+//
+//  * One bit per site.  v(x, y) = ((h(x, y) - x - y) / 2) mod 2 (in a gauge of
+//    the tile): v keeps its value along an up step (slope bit 1) and changes
+//    along a down step.  An attempt's site is a local minimum iff
+//    v(left) = v(above) != v = v(right) = v(below), a local maximum iff
+//    v(left) = v(above) = v != v(right) = v(below), and either flip is the flip
+//    of this one bit.
+//  * Cells in registers.  Under DT the cell grid stands still and a round's
+//    attempts all lie in the same quadrant of their cells, so a lane keeps a
+//    stack of cells, two to a register: register [pair][qx][qy] holds the
+//    4 x 4 sites of quadrant (qx, qy) of one cell in its low half and of the
+//    cell half a stack further down in its high half, bit 4 row + column, which
+//    is the order of the lane draw's site index.  A round forms the four
+//    neighbours of all 32 sites by shifts (the neighbouring quadrants are other
+//    registers of the lane, of the lane beside it, or of the lane row above or
+//    below), tests them all at once and lets the drawn sites' bits through:
+//    17 instructions for two attempts, no LDS and, inside a wave, no barrier.
+//    Column -1, column D, row -1 and row D never change during the step.
+//  * Random fields two cells to a register in the same halves: the drawn
+//    sites' bits are one packed 16-bit shift, the acceptance masks a packed
+//    subtraction and sign.
+//
+// The step is bound by vector issue: 90 % VALU busy at p = 1 (95 % with
+// draws), where the row-paired LDS kernel it replaces was bound by LDS and
+// issue together (73 % and 69 %).  D = 256, L = 2^16, per launch: p = 1 0.863
+// -> 0.435 ms (28.6 -> 14.3 VALU instructions per wave-attempt), p = 0.95
+// 0.94 -> 0.72 ms; D = 128 p = 1 0.90 -> 0.47 ms, p = 1/2 0.96 -> 0.65 ms; 64
+// tiles (L = 4096) 31.1 -> 25 us.  Two waves per tile rather than one (which
+// needs no barrier and fewer instructions): a single wave holds 16 cells a
+// lane, 168 registers with spills, three waves per SIMD, 66-77 % VALU busy and
+// 0.51 ms (0.97 with draws).
 #pragma once
 
 #include "kernels.hpp"
@@ -153,7 +185,43 @@ __device__ __forceinline__ uint32_t running_xor(uint32_t x)
     return x ^ (x << 16);
 }
 
-template <int MODE, int LD, int NW>
+// SHARED: other workgroups of the same launch read and write the lattice (the
+// batch kernel).  Words then go past the caches that are private to a die.
+template <bool SHARED>
+__device__ __forceinline__ uint32_t load_word(const char *p)
+{
+    if (SHARED)
+        return __hip_atomic_load(reinterpret_cast<const uint32_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return *reinterpret_cast<const uint32_t *>(p);
+}
+
+template <bool SHARED>
+__device__ __forceinline__ uint4 load_words(const char *p)
+{
+    if (SHARED) {
+        const uint64_t a = __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t b = __hip_atomic_load(reinterpret_cast<const uint64_t *>(p) + 1, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        return make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
+    }
+    return *reinterpret_cast<const uint4 *>(p);
+}
+
+template <bool SHARED>
+__device__ __forceinline__ void store_words(char *p, const uint32_t (&w)[4])
+{
+    if (SHARED) {
+        __hip_atomic_store(reinterpret_cast<uint64_t *>(p), w[0] | (uint64_t)w[1] << 32, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(reinterpret_cast<uint64_t *>(p) + 1, w[2] | (uint64_t)w[3] << 32, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        *reinterpret_cast<uint4 *>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+}
+
+template <int MODE, int LD, int NW, bool SHARED>
 __device__ __forceinline__ void sweep_dt_cells(const StepArgs &A, uint32_t *smem, uint32_t tile)
 {
     using S = CellShape<LD, NW>;
@@ -163,8 +231,12 @@ __device__ __forceinline__ void sweep_dt_cells(const StepArgs &A, uint32_t *smem
     uint32_t *table = smem + S::PLANE;
     uint32_t *edge_a = table + S::TABLE;     // last row of cells of each wave, by quadrant column
     uint32_t *edge_b = edge_a + 2 * NW * NCX;  // first row of cells of each wave
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = NW > 1 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0u;
+    // opaque: in the batch kernel's loop the compiler otherwise keeps what it
+    // derives from the lane's number in registers across all items
+    uint32_t tid = threadIdx.x;
+    if (SHARED) asm volatile("" : "+v"(tid));
+    const uint32_t lane = tid & 63u;
+    const uint32_t wave = NW > 1 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6)) : 0u;
     const uint32_t cx = lane & (NCX - 1u), g = lane >> S::LOG2NCX, G = wave * S::GPW + g;
     const uint32_t i = cx & 3u, k = cx >> 2;  // place in the quad, word column
     const uint32_t tx = tile & ((1u << A.log2ntx) - 1u), ty = tile >> A.log2ntx;
@@ -173,23 +245,58 @@ __device__ __forceinline__ void sweep_dt_cells(const StepArgs &A, uint32_t *smem
     const uint32_t offx = X0 & 31u, offy = Y0 & 3u, bx0 = X0 >> 5, by0 = Y0 >> 2;
     const uint32_t band_log2 = A.nbx_log2 + 5u;  // bytes of a band; the lattice is at most 2^32 bytes
     char *const base = reinterpret_cast<char *>(A.words);
-    auto word_at = [&](uint32_t off) { return *reinterpret_cast<const uint32_t *>(base + off); };
+    auto word_at = [&](uint32_t off) { return load_word<SHARED>(base + off); };
     auto block_off = [&](uint32_t kk) { return ((bx0 + kk) & A.nbx_mask) << 5; };
 
-    // ---- columns 0 and D, by row quads: lane l takes rows 4 l .. 4 l + 3
+    // ---- loads, all in flight together: columns 0 and D of the row quads 4 l .. 4 l + 3 (lane l), row 0,
+    // the row the lane's first one is reached from, the sy words of the lane's rows (the four lanes of a quad
+    // take the four rows of a row quad), and the row past the domain
+    const uint32_t lq = lane & (S::D / 4u - 1u);  // the upper lanes of D = 128 repeat the lower ones' loads
+    const uint32_t q0 = 2u * G * S::CPT;          // the lane's first row quad
+    const uint32_t row0 = ((Y0 >> 2) << band_log2) + ((Y0 & 3u) << 2);
+    const uint32_t kb0 = block_off(k), kb1 = block_off(k + 1u);
+    uint32_t c0x[4], c0y[4], cdy[4], across, first[2], sy0[2], syd[2], sy[2 * S::CPT][2];
+    const uint32_t from = G == 0u ? 0u : 4u * q0 - 1u;
     {
-        uint32_t nx = 0u, ny = 0u, nd = 0u;
-        const uint32_t lq = lane & (S::D / 4u - 1u);
-        const uint32_t o0 = block_off(0u), od = block_off(KW);
+        const char *const col0 = base + block_off(0u), *const cold = base + block_off(KW);
 #pragma unroll
         for (uint32_t r = 0; r < 4; ++r) {
-            const uint32_t y = (Y0 + 4u * lq + r) & A.L_mask;
-            const uint32_t row = ((y >> 2) << band_log2) + ((y & 3u) << 2);
-            nx |= ((word_at(row + o0) >> offx) & 1u) << r;
-            ny |= ((word_at(row + o0 + 16u) >> offx) & 1u) << r;
-            nd |= ((word_at(row + od + 16u) >> offx) & 1u) << r;
+            const uint32_t off = ((lq + ((Y0 + r) >> 2)) & A.nby_mask) << band_log2, srow = ((Y0 + r) & 3u) << 2;
+            c0x[r] = load_word<SHARED>(col0 + srow + off);
+            c0y[r] = load_word<SHARED>(col0 + (srow + 16u) + off);
+            cdy[r] = load_word<SHARED>(cold + (srow + 16u) + off);
         }
-        // v(0, y) from v(0, 0) = 0 down: a step of the surface up keeps v
+        across = word_at(row0 + block_off(min(lane, KW)));
+        const uint32_t yf = (Y0 + from) & A.L_mask;
+        const uint32_t off = ((yf >> 2) << band_log2) + ((yf & 3u) << 2);
+        first[0] = word_at(off + kb0);
+        first[1] = word_at(off + kb1);
+        sy0[0] = word_at(row0 + 16u + kb0);
+        sy0[1] = word_at(row0 + 16u + kb1);
+        const uint32_t band0 = ((Y0 + i) >> 2) + q0, rowb = (((Y0 + i) & 3u) << 2) + 16u;
+        const uint32_t o0 = rowb + kb0, o1 = rowb + kb1;
+#pragma unroll
+        for (uint32_t b = 0; b < 2u * S::CPT; ++b) {
+            const uint32_t bo = ((band0 + b) & A.nby_mask) << band_log2;
+            sy[b][0] = word_at(bo + o0);
+            sy[b][1] = word_at(bo + o1);
+        }
+        const uint32_t yd = (Y0 + S::D) & A.L_mask;
+        const uint32_t offd = ((yd >> 2) << band_log2) + ((yd & 3u) << 2) + 16u;
+        syd[0] = word_at(offd + kb0);
+        syd[1] = word_at(offd + kb1);
+    }
+
+    // ---- v in columns 0, -1 and D
+    {
+        uint32_t nx = 0u, ny = 0u, nd = 0u;
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            nx |= __builtin_amdgcn_ubfe(c0x[r], offx, 1) << r;
+            ny |= __builtin_amdgcn_ubfe(c0y[r], offx, 1) << r;
+            nd |= __builtin_amdgcn_ubfe(cdy[r], offx, 1) << r;
+        }
+        // down a column from 0 in row 0: a step of the surface up keeps v
         auto down = [&](uint32_t n) {
             uint32_t e = ~n & 15u;
             if (lane == 0u) e &= ~1u;
@@ -206,15 +313,13 @@ __device__ __forceinline__ void sweep_dt_cells(const StepArgs &A, uint32_t *smem
         };
         const uint32_t n0 = down(ny);
         // v(D, 0) from v(0, 0) along row 0
-        uint32_t w = 0u;
-        if (lane <= KW) w = word_at(((Y0 >> 2) << band_log2) + ((Y0 & 3u) << 2) + block_off(lane));
-        if (lane == 0u) w &= (~0u << offx) << 1;
-        if (lane == KW) w &= (2u << offx) - 1u;
-        const uint32_t across = (uint32_t)__popcll(__ballot((__popc(w) & 1) != 0)) & 1u;
-        const uint32_t nr = down(nd) ^ (across ? 15u : 0u);
+        if (lane == 0u) across &= (~0u << offx) << 1;
+        if (lane == KW) across &= (2u << offx) - 1u;
+        const uint64_t odd = __ballot(lane <= KW && (__popc(across) & 1) != 0);
+        const uint32_t nr = down(nd) ^ (((uint32_t)__popcll(odd) & 1u) ? 15u : 0u);
         const uint32_t nl = n0 ^ nx ^ 15u;
         auto spread = [](uint32_t n) { return (n & 1u) | (n & 2u) << 3 | (n & 4u) << 6 | (n & 8u) << 9; };
-        if (lane < S::D / 4u) {  // the other lanes of D = 128 repeat the first ones' loads
+        if (lane < S::D / 4u) {
             table[lane] = n0;
             table[64u + lane] = spread(nl) << 3;
             table[128u + lane] = spread(nr);
@@ -227,62 +332,54 @@ __device__ __forceinline__ void sweep_dt_cells(const StepArgs &A, uint32_t *smem
         wave_order();
     }
 
-    // ---- the lane's cells: row quad B of its column as four rows of a quad of lanes
+    // ---- the lane's cells
     const uint32_t s1 = (i & 1u) ? 0x03070105u : 0x06020400u;
     const uint32_t s2 = (i & 2u) ? 0x03020706u : 0x05040100u;
     uint32_t q[NP][2][2];  // [pair][quadrant column][quadrant row]
     uint32_t halo[NP][2];  // column -1 (lanes of the first column) or D (of the last)
-    const uint32_t q0 = 2u * G * S::CPT;  // the lane's first row quad
+    uint32_t vhalo[2];     // by quadrant column: row -1 in bits 28-31, row D in bits 0-3
     {
-        const uint32_t kb0 = block_off(k), kb1 = block_off(k + 1u);
-        const uint32_t band0 = ((Y0 + i) >> 2) + q0, rowb = ((Y0 + i) & 3u) << 2;
-        const uint32_t keep = k == 0u ? ~1u : ~0u;
-        const uint32_t htab = (cx == NCX - 1u ? 128u : 64u) + q0;
-        auto row_word = [&](uint32_t b, uint32_t plane_off) {
-            const uint32_t off = ((b & A.nby_mask) << band_log2) + rowb + plane_off;
-            return __builtin_amdgcn_alignbit(word_at(off + kb1), word_at(off + kb0), offx);
-        };
+        // the row above the lane's first one, along the row from column 0
         constexpr uint64_t seg4 = NCX == 32 ? 0xFFFFFFF0FFFFFFF0ull : 0xFFF0FFF0FFF0FFF0ull;
         constexpr uint64_t seg8 = NCX == 32 ? 0xFFFFFF00FFFFFF00ull : 0xFF00FF00FF00FF00ull;
+        const uint32_t a = running_xor(__builtin_amdgcn_alignbit(first[1], first[0], offx) & (k == 0u ? ~1u : ~0u));
+        uint64_t s = __ballot((int)a < 0);
+        s ^= (s << 4) & seg4;
+        s ^= (s << 8) & seg8;
+        if (NCX == 32) s ^= (s << 16) & 0xFFFF0000FFFF0000ull;
+        s = (s << 4) & seg4;
+        const uint32_t c = __builtin_amdgcn_inverse_ballot_w64(s) ? 0x55555555u : 0xAAAAAAAAu;
+        uint32_t v = bit3<0x96>(a, c, (uint32_t)__builtin_amdgcn_sbfe((int)table[from >> 2], from & 3u, 1));
+        if (G == 0u) v = ~(v ^ __builtin_amdgcn_alignbit(sy0[1], sy0[0], offx));
+        const uint32_t top = (v >> (8u * i)) & 255u;
+        // then down the rows: byte r of p is the lane's eight columns of row r of the quad
+        uint32_t prev = v << (24u - 8u * i);
+        uint32_t p[2 * S::CPT];
+#pragma unroll
+        for (uint32_t b = 0; b < 2u * S::CPT; ++b) {
+            uint32_t x = quad_transpose(__builtin_amdgcn_alignbit(sy[b][1], sy[b][0], offx), s1, s2);
+            x ^= x << 8;
+            x ^= x << 16;
+            prev = bit3<0x96>(x, __builtin_amdgcn_perm(prev, prev, 0x07070707u), 0x00FF00FFu);
+            p[b] = swap_nibbles(prev);
+        }
+        const uint32_t bot = ~((prev >> 24) ^ (__builtin_amdgcn_alignbit(syd[1], syd[0], offx) >> (8u * i))) & 255u;
+        uint8_t *bytes = reinterpret_cast<uint8_t *>(plane);
+        if (G == 0u) bytes[4u + cx] = (uint8_t)top;
+        if (G == S::NG - 1u) bytes[4u * ((S::D + 1u) * PITCH + 1u) + cx] = (uint8_t)bot;
+        vhalo[0] = top << 28 | (bot & 15u);
+        vhalo[1] = (top >> 4) << 28 | bot >> 4;
+        const uint32_t htab = (cx == NCX - 1u ? 128u : 64u) + q0;
 #pragma unroll
         for (int j = 0; j < NP; ++j)
 #pragma unroll
             for (int qy = 0; qy < 2; ++qy) {
-                uint32_t p[2], h[2];
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const uint32_t b = 2u * (uint32_t)(j + t * NP) + (uint32_t)qy;
-                    const uint32_t a = running_xor(row_word(band0 + b, 0u) & keep);
-                    uint64_t s = __ballot((int)a < 0);
-                    s ^= (s << 4) & seg4;
-                    s ^= (s << 8) & seg8;
-                    if (NCX == 32) s ^= (s << 16) & 0xFFFF0000FFFF0000ull;
-                    s = (s << 4) & seg4;
-                    const uint32_t c = __builtin_amdgcn_inverse_ballot_w64(s) ? 0x55555555u : 0xAAAAAAAAu;
-                    const uint32_t v = bit3<0x96>(a, c, (uint32_t)__builtin_amdgcn_sbfe((int)table[q0 + b], i, 1));
-                    // rows -1 and D
-                    if (b == 0u && G == 0u && i == 0u) plane[k + 1u] = ~(v ^ row_word(band0, 16u));
-                    if (b == 2u * S::CPT - 1u && G == S::NG - 1u && i == 3u) {
-                        const uint32_t y = (Y0 + S::D) & A.L_mask;
-                        const uint32_t off = ((y >> 2) << band_log2) + ((y & 3u) << 2) + 16u;
-                        plane[(S::D + 1u) * PITCH + k + 1u] =
-                            ~(v ^ __builtin_amdgcn_alignbit(word_at(off + kb1), word_at(off + kb0), offx));
-                    }
-                    p[t] = swap_nibbles(quad_transpose(v, s1, s2));
-                    h[t] = table[htab + b];
-                }
-                q[j][0][qy] = __builtin_amdgcn_perm(p[1], p[0], 0x06040200u);
-                q[j][1][qy] = __builtin_amdgcn_perm(p[1], p[0], 0x07050301u);
-                halo[j][qy] = h[0] | h[1] << 16;
+                const uint32_t lo = p[2 * j + qy], hi = p[2 * (j + NP) + qy];
+                q[j][0][qy] = __builtin_amdgcn_perm(hi, lo, 0x06040200u);
+                q[j][1][qy] = __builtin_amdgcn_perm(hi, lo, 0x07050301u);
+                halo[j][qy] = table[htab + 2u * (uint32_t)j + (uint32_t)qy] |
+                              table[htab + 2u * (uint32_t)(j + NP) + (uint32_t)qy] << 16;
             }
-    }
-    wave_order();
-    uint32_t vhalo[2];  // by quadrant column: row -1 in bits 28-31, row D in bits 0-3
-    {
-        const uint8_t *bytes = reinterpret_cast<const uint8_t *>(plane);
-        const uint32_t top = bytes[4u + cx], bot = bytes[4u * ((S::D + 1u) * PITCH + 1u) + cx];
-        vhalo[0] = top << 28 | (bot & 15u);
-        vhalo[1] = (top >> 4) << 28 | bot >> 4;
     }
     if (NW > 1) {
 #pragma unroll
@@ -441,6 +538,31 @@ __device__ __forceinline__ void sweep_dt_cells(const StepArgs &A, uint32_t *smem
         }
     }
 
+    // ---- the window's outer blocks, which keep bits of other domains: loads in flight
+    constexpr uint32_t RIM = 2u * S::NB + 2u * (KW - 1u), TURNS = (RIM + 64u * NW - 1u) / (64u * NW);
+    auto rim_block = [&](uint32_t t, uint32_t &b, uint32_t &kk) {
+        if (t < 2u * S::NB) {
+            b = t >> 1;
+            kk = (t & 1u) ? KW : 0u;
+        } else {
+            const uint32_t u = min(t, RIM - 1u) - 2u * S::NB;
+            b = (u & 1u) ? S::NB - 1u : 0u;
+            kk = 1u + (u >> 1);
+        }
+    };
+    auto block_at = [&](uint32_t b, uint32_t kk) {
+        return base + ((((by0 + b) & A.nby_mask) << band_log2) + block_off(kk));
+    };
+    uint4 rim[TURNS][2];
+#pragma unroll
+    for (uint32_t n = 0; n < TURNS; ++n) {
+        uint32_t b, kk;
+        rim_block(tid + 64u * NW * n, b, kk);
+        const char *p = block_at(b, kk);
+        rim[n][0] = load_words<SHARED>(p);
+        rim[n][1] = load_words<SHARED>(p + 16);
+    }
+
     // ---- back to row words in LDS
 #pragma unroll
     for (int j = 0; j < NP; ++j)
@@ -457,48 +579,62 @@ __device__ __forceinline__ void sweep_dt_cells(const StepArgs &A, uint32_t *smem
     else
         wave_order();
 
-    // ---- slopes of the window's blocks, one block per lane and turn
-    for (uint32_t t = threadIdx.x; t < S::NWX * S::NB; t += 64u * NW) {
-        const uint32_t b = t / S::NWX, kk = t % S::NWX;
-        const uint32_t off = (((by0 + b) & A.nby_mask) << band_log2) + block_off(kk);
-        uint4 *px = reinterpret_cast<uint4 *>(base + off), *py = px + 1;
-        const bool edge = kk == 0u || kk == KW || b == 0u || b == S::NB - 1u;
-        uint4 ox = make_uint4(0u, 0u, 0u, 0u), oy = ox;
-        if (edge) {
-            ox = *px;
-            oy = *py;
-        }
-        uint32_t wl[5], wv[5];  // v of the block's columns and of those one to the left, rows -1 .. 3 of the band
+    // ---- the slopes of a block: differences of v along the row and down the column
+    auto slopes = [&](uint32_t b, uint32_t kk, auto clamp_c, uint32_t (&nx)[4], uint32_t (&ny)[4]) {
+        constexpr bool CLAMP = decltype(clamp_c)::value;
+        uint32_t above = 0u;
 #pragma unroll
         for (int r = 0; r < 5; ++r) {
             int y = (int)(4u * b) + r - (int)offy;  // LDS row of domain row y - 1
-            y = min(max(y, 0), (int)S::D + 1);
-            const uint32_t w0 = plane[(uint32_t)y * PITCH + kk], w1 = plane[(uint32_t)y * PITCH + kk + 1u];
-            wl[r] = __builtin_amdgcn_alignbit(w1, w0, 31u - offx);
-            wv[r] = __builtin_amdgcn_alignbit(w1 >> (31u - offx), wl[r], 1u);
+            if (CLAMP) y = min(max(y, 0), (int)S::D + 1);
+            const uint32_t *w = plane + (uint32_t)y * PITCH + kk;
+            const uint32_t left = __builtin_amdgcn_alignbit(w[1], w[0], 31u - offx);  // one column to the left
+            const uint32_t v = __builtin_amdgcn_alignbit(w[1] >> (31u - offx), left, 1u);
+            if (r > 0) {
+                nx[r - 1] = ~(v ^ left);
+                ny[r - 1] = ~(v ^ above);
+            }
+            above = v;
         }
-        uint32_t cy = kk == 0u ? ~0u << offx : (kk == KW ? (1u << offx) - 1u : ~0u);
-        uint32_t cxm = kk == KW ? (2u << offx) - 1u : cy;
+    };
+    constexpr uint32_t INNER = (S::NB - 2u) * (KW - 1u);
+    for (uint32_t t = tid; t < INNER; t += 64u * NW) {
+        const uint32_t b = 1u + t / (KW - 1u), kk = 1u + t % (KW - 1u);
         uint32_t nx[4], ny[4];
-        const uint32_t wx[4] = {ox.x, ox.y, ox.z, ox.w}, wy[4] = {oy.x, oy.y, oy.z, oy.w};
+        slopes(b, kk, std::false_type(), nx, ny);
+        char *p = block_at(b, kk);
+        store_words<SHARED>(p, nx);
+        store_words<SHARED>(p + 16, ny);
+    }
+#pragma unroll
+    for (uint32_t n = 0; n < TURNS; ++n) {
+        const uint32_t t = tid + 64u * NW * n;
+        if (t >= RIM) break;
+        uint32_t b, kk;
+        rim_block(t, b, kk);
+        uint32_t nx[4], ny[4];
+        slopes(b, kk, std::true_type(), nx, ny);
+        const uint32_t my = kk == 0u ? ~0u << offx : (kk == KW ? (1u << offx) - 1u : ~0u);
+        const uint32_t mx = kk == KW ? (2u << offx) - 1u : my;
+        const uint32_t wx[4] = {rim[n][0].x, rim[n][0].y, rim[n][0].z, rim[n][0].w};
+        const uint32_t wy[4] = {rim[n][1].x, rim[n][1].y, rim[n][1].z, rim[n][1].w};
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int y = (int)(4u * b) + r - (int)offy;  // domain row
-            const uint32_t mx = y >= 0 && y < (int)S::D ? cxm : 0u, my = y >= 0 && y <= (int)S::D ? cy : 0u;
-            nx[r] = select_bits(mx, ~(wv[r + 1] ^ wl[r + 1]), wx[r]);
-            ny[r] = select_bits(my, ~(wv[r + 1] ^ wv[r]), wy[r]);
+            const uint32_t y = 4u * b + (uint32_t)r - offy;  // domain row
+            nx[r] = select_bits(y < S::D ? mx : 0u, nx[r], wx[r]);
+            ny[r] = select_bits(y <= S::D ? my : 0u, ny[r], wy[r]);
         }
-        *px = make_uint4(nx[0], nx[1], nx[2], nx[3]);
-        *py = make_uint4(ny[0], ny[1], ny[2], ny[3]);
+        char *p = block_at(b, kk);
+        store_words<SHARED>(p, nx);
+        store_words<SHARED>(p + 16, ny);
     }
 }
 
 template <int MODE, int LD, int NW>
-__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3)))
-step_dt_cells_kernel(StepArgs A)
+__global__ void __launch_bounds__(64 * NW) step_dt_cells_kernel(StepArgs A)
 {
     extern __shared__ uint32_t smem[];
-    sweep_dt_cells<MODE, LD, NW>(A, smem, blockIdx.x);
+    sweep_dt_cells<MODE, LD, NW, false>(A, smem, blockIdx.x);
 }
 
 }  // namespace okpz

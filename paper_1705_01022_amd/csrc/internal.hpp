@@ -271,11 +271,16 @@ inline bool dt_cells_shape(const okpz_params &p)
            (p.dom_x == 128u || p.dom_x == 256u) && p.cell_x == 8u && p.cell_y == 8u;
 }
 
-// Waves per tile of that step.
-inline uint32_t dt_cells_waves(uint32_t threads, uint64_t ntiles, uint32_t cus)
+// Waves per tile of that step: one for 128-site domains (two leave a lane one
+// pair of cells: L = 2^16 at p = 1 0.79 ms a launch against 0.47); for 256-site
+// domains two, or four when a step has fewer tiles than four per compute unit
+// (p = 1, two against four: 1024 tiles 48 against 51 us, 256 tiles 34 against
+// 29, 64 tiles 33 against 28), or what the workgroup size asks for.
+inline uint32_t dt_cells_waves(uint32_t dom, uint32_t threads, uint64_t ntiles, uint32_t cus)
 {
-    if (threads) return threads / 64u;
-    return ntiles < 4ull * cus ? 4u : 1u;
+    if (dom == 128u) return 1u;
+    if (threads) return threads <= 128u ? 2u : 4u;
+    return ntiles < 4ull * cus ? 4u : 2u;
 }
 
 inline StepArgs base_args(const okpz_lattice *lat, const LaneShape &ls, double pd, double qr)

@@ -116,17 +116,14 @@ int launch_dt_cells_shape(int mode, uint32_t ntiles, hipStream_t st, const StepA
 }
 
 // DT on square 128- or 256-site domains of 8 x 8-site cells: the domain in
-// registers, `nw` waves per tile.
-int launch_dt_cells(uint32_t nw, uint32_t ntiles, hipStream_t st, const StepArgs &a, bool accept)
+// registers.
+int launch_dt_cells(const okpz_lattice *lat, uint32_t ntiles, const StepArgs &a, bool accept)
 {
     const int mode = accept ? kDraw : a.flip_table == kFlipMin ? kDeposit : kSure;
-    if (a.Dx == 128u)  // two cells a lane at least
-        return nw == 1 ? launch_dt_cells_shape<7, 1>(mode, ntiles, st, a) : launch_dt_cells_shape<7, 2>(mode, ntiles, st, a);
-    switch (nw) {
-    case 1: return launch_dt_cells_shape<8, 1>(mode, ntiles, st, a);
-    case 2: return launch_dt_cells_shape<8, 2>(mode, ntiles, st, a);
-    case 4: return launch_dt_cells_shape<8, 4>(mode, ntiles, st, a);
-    default: return launch_dt_cells_shape<8, 8>(mode, ntiles, st, a);
+    switch (dt_cells_waves(a.Dx, lat->threads, ntiles, lat->cus)) {
+    case 1: return launch_dt_cells_shape<7, 1>(mode, ntiles, lat->stream, a);
+    case 2: return launch_dt_cells_shape<8, 2>(mode, ntiles, lat->stream, a);
+    default: return launch_dt_cells_shape<8, 4>(mode, ntiles, lat->stream, a);
     }
 }
 
@@ -182,7 +179,7 @@ int launch_step(okpz_lattice *lat, const StepArgs &a, bool accept)
     const uint32_t span = a.dev_db ? 1u : 2u;  // dead border: every dom_x x dom_y tile in one step
     const uint32_t ntiles = (p.L / (span * p.dom_x)) * (p.L / (span * p.dom_y));
     if (dt_cells_shape(p)) {
-        const int rc = launch_dt_cells(dt_cells_waves(lat->threads, ntiles, lat->cus), ntiles, lat->stream, a, accept);
+        const int rc = launch_dt_cells(lat, ntiles, a, accept);
         if (rc != OKPZ_OK) return rc;
         HIP_TRY(hipGetLastError());
         return OKPZ_OK;

@@ -258,21 +258,21 @@ __attribute__((amdgpu_waves_per_eu((SCHEME != kDB && CPT <= 4) || LD > 0 ? 6 : 1
 batch_kernel(BatchArgs B)
 {
     extern __shared__ uint32_t smem[];
-    batch_items<false>(B, [&](const BatchSlot &S, const StepArgs &A, uint32_t tile) {
+    batch_items<(LD > 0)>(B, [&](const BatchSlot &S, const StepArgs &A, uint32_t tile) {
         if constexpr (LD > 0 && SCHEME != kDB) {
             if (A.Dx == 256u) {
                 if (S.accept)
-                    sweep_dt_rows<SCHEME, true, CPT, 8, 3>(A, smem, tile);
+                    sweep_dt_rows<SCHEME, true, CPT, 8, 3, true>(A, smem, tile);
                 else
-                    sweep_dt_rows<SCHEME, false, CPT, 8, 3>(A, smem, tile);
+                    sweep_dt_rows<SCHEME, false, CPT, 8, 3, true>(A, smem, tile);
             } else {
                 if (S.accept)
-                    sweep_dt_rows<SCHEME, true, CPT, 7, 3>(A, smem, tile);
+                    sweep_dt_rows<SCHEME, true, CPT, 7, 3, true>(A, smem, tile);
                 else
-                    sweep_dt_rows<SCHEME, false, CPT, 7, 3>(A, smem, tile);
+                    sweep_dt_rows<SCHEME, false, CPT, 7, 3, true>(A, smem, tile);
             }
         } else if constexpr (LD > 0) {
-            sweep_db_rows<FL == 4, CPT, LD, 3>(A, smem, tile);
+            sweep_db_rows<FL == 4, CPT, LD, 3, true>(A, smem, tile);
         } else if constexpr (COLS && FL > 0) {
             sweep_db_columns<FL == 4, CPT, FL>(A, smem, tile);
         } else if constexpr (COLS) {

@@ -185,42 +185,6 @@ __device__ __forceinline__ uint32_t running_xor(uint32_t x)
     return x ^ (x << 16);
 }
 
-// SHARED: other workgroups of the same launch read and write the lattice (the
-// batch kernel).  Words then go past the caches that are private to a die.
-template <bool SHARED>
-__device__ __forceinline__ uint32_t load_word(const char *p)
-{
-    if (SHARED)
-        return __hip_atomic_load(reinterpret_cast<const uint32_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return *reinterpret_cast<const uint32_t *>(p);
-}
-
-template <bool SHARED>
-__device__ __forceinline__ uint4 load_words(const char *p)
-{
-    if (SHARED) {
-        const uint64_t a = __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-        const uint64_t b = __hip_atomic_load(reinterpret_cast<const uint64_t *>(p) + 1, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-        return make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
-    }
-    return *reinterpret_cast<const uint4 *>(p);
-}
-
-template <bool SHARED>
-__device__ __forceinline__ void store_words(char *p, const uint32_t (&w)[4])
-{
-    if (SHARED) {
-        __hip_atomic_store(reinterpret_cast<uint64_t *>(p), w[0] | (uint64_t)w[1] << 32, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(reinterpret_cast<uint64_t *>(p) + 1, w[2] | (uint64_t)w[3] << 32, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-        *reinterpret_cast<uint4 *>(p) = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-}
-
 template <int MODE, int LD, int NW, bool SHARED>
 __device__ __forceinline__ void sweep_dt_cells(const StepArgs &A, uint32_t *smem, uint32_t tile)
 {

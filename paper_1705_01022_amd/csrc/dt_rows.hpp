@@ -25,7 +25,7 @@ __host__ __device__ constexpr uint32_t rowpair_dt_lds_words()
 // stacked vertically, so the lanes of one instruction sit side by side in
 // one or two cell rows.  Lane-draw fields are 2^FL bits (16 with acceptance
 // prefixes, 4 without), the rounds of one Philox block unrolled.
-template <int SCHEME, bool ACCEPT, int CPT, int LD, int LC>
+template <int SCHEME, bool ACCEPT, int CPT, int LD, int LC, bool SHARED>
 __device__ __forceinline__ void sweep_dt_rows(const StepArgs &A, uint32_t *smem, uint32_t tile)
 {
     using S = RowPairShape<LD, LC, true>;
@@ -38,7 +38,8 @@ __device__ __forceinline__ void sweep_dt_rows(const StepArgs &A, uint32_t *smem,
     constexpr uint32_t P = S::P;
     static_assert(SBITS + (ACCEPT ? 8 : 0) <= F && (ACCEPT || SBITS == F), "field width");
     static_assert(SCHEME == kDT || SCHEME == kDTR, "DT or DTr");
-    const uint32_t tid = threadIdx.x;
+    uint32_t tid = threadIdx.x;
+    if (SHARED) asm volatile("" : "+v"(tid));  // opaque: nothing is kept across the items of a batch
     uint32_t *lds = smem;
 
     const uint32_t tx = tile & ((1u << A.log2ntx) - 1u), ty = tile >> A.log2ntx;
@@ -47,7 +48,8 @@ __device__ __forceinline__ void sweep_dt_rows(const StepArgs &A, uint32_t *smem,
     // linear index of domain site (0, 0), counted from LDS address 0
     const uint32_t origin = (Y0 & 3u) * S::ROW + (X0 & 31u) + 8u * lds_address(lds);
 
-    copy_window_rows<true, P, S::PITCH>(A, lds, X0 >> 5, Y0 >> 2);
+    constexpr uint32_t NTC = S::NCX * S::NCX / CPT;  // the workgroup's lanes, or fewer
+    load_window_rows<S, NTC, SHARED>(A, lds, X0 >> 5, Y0 >> 2);
 
     // lanes past the domain's cells (a batch sizes its workgroups for its
     // largest domains) only stage the window and keep the barriers; they
@@ -100,7 +102,7 @@ __device__ __forceinline__ void sweep_dt_rows(const StepArgs &A, uint32_t *smem,
             __syncthreads();
         }
     }
-    copy_window_rows<false, P, S::PITCH>(A, lds, X0 >> 5, Y0 >> 2);
+    store_window_rows<S, NTC, SHARED>(A, lds, X0 >> 5, Y0 >> 2);
 }
 
 // The DT / DTr device-step kernel on the row-paired window.
@@ -109,7 +111,7 @@ __global__ void __launch_bounds__(kMaxStepThreads) __attribute__((amdgpu_waves_p
 step_dt_rows_kernel(StepArgs A)
 {
     extern __shared__ uint32_t smem[];
-    sweep_dt_rows<SCHEME, ACCEPT, CPT, LD, LC>(A, smem, blockIdx.x);
+    sweep_dt_rows<SCHEME, ACCEPT, CPT, LD, LC, false>(A, smem, blockIdx.x);
 }
 
 }  // namespace okpz

@@ -197,13 +197,25 @@ __device__ __forceinline__ void flip_masks(uint32_t s, uint32_t &m1, uint32_t &m
     asm("v_lshlrev_b32 %0, %1, 3" : "=v"(m3) : "v"(s));
 }
 
-template <bool ACCEPT, uint32_t P, uint32_t PITCH>
-__device__ __forceinline__ void attempt_rows(const StepArgs &A, uint32_t s, uint32_t pre, bool enable, uint32_t rho,
-                                             uint32_t cell, uint32_t tile)
+// The four slope words of the site at linear index s.
+struct SlopeWords {
+    uint32_t w0, w1, y0, y1;
+};
+
+template <uint32_t P, uint32_t PITCH>
+__device__ __forceinline__ SlopeWords read_rows(uint32_t s)
 {
     lds_word *px = lds_at((s >> 3) & ~3u);
-    const uint32_t w0 = px[0], w1 = px[1];
-    const uint32_t y0 = px[P], y1 = px[P + PITCH];
+    return SlopeWords{px[0], px[1], px[P], px[P + PITCH]};
+}
+
+// Decides on the words read and flips.
+template <bool ACCEPT, uint32_t P, uint32_t PITCH>
+__device__ __forceinline__ void decide_rows(const StepArgs &A, const SlopeWords &v, uint32_t s, uint32_t pre,
+                                            bool enable, uint32_t rho, uint32_t cell, uint32_t tile)
+{
+    lds_word *px = lds_at((s >> 3) & ~3u);
+    const uint32_t w0 = v.w0, w1 = v.w1, y0 = v.y0, y1 = v.y1;
     const uint32_t d = __builtin_amdgcn_ubfe(y1, s, 1);
     bool flip;
     if (ACCEPT) {
@@ -221,7 +233,8 @@ __device__ __forceinline__ void attempt_rows(const StepArgs &A, uint32_t s, uint
         const int rel = mad_i24((int)d, -A.pq_delta, (int)pre);
         const int t = (rel & sel) | (0x7fffffff & ~sel);
         flip = enable && t < (int)A.Q_hi;
-        if (enable && t == (int)A.Q_hi) {  // the prefix ties: the low 32 bits of the variate decide
+        const bool tie = enable && t == (int)A.Q_hi;  // the low 32 bits of the variate decide
+        if (tie) {
             // the tie counter formed here, where the rare branch runs: as a
             // loop-invariant value the compiler would keep its first Philox
             // products in registers for the whole sweep
@@ -246,6 +259,14 @@ __device__ __forceinline__ void attempt_rows(const StepArgs &A, uint32_t s, uint
         if (m3 == 0x80000000u)  // x is bit 31: sx(x+1) is bit 0 of the next word
             __hip_atomic_fetch_xor(&px[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
+}
+
+// Both in one: an attempt that nothing comes between.
+template <bool ACCEPT, uint32_t P, uint32_t PITCH>
+__device__ __forceinline__ void attempt_rows(const StepArgs &A, uint32_t s, uint32_t pre, bool enable, uint32_t rho,
+                                             uint32_t cell, uint32_t tile)
+{
+    decide_rows<ACCEPT, P, PITCH>(A, read_rows<P, PITCH>(s), s, pre, enable, rho, cell, tile);
 }
 
 // (du + cu) mod D, the column of a draw in the shifted cell grid; at D = 256
@@ -356,7 +377,8 @@ __device__ __forceinline__ void sweep_db_rows(const StepArgs &A, uint32_t *smem,
     auto corner_of = [](uint32_t f) { return (f & ((1u << S::SBITS) - 1u)) == (1u << S::SBITS) - 1u; };
 
     BlockDraw bd = {0u, 0u, 0u, 0u};
-    uint32_t f16 = next_block_field(A, bd, 0u, tile);
+    const u32x4 draws = block_draws(A, tile);
+    uint32_t f16 = next_block_field(draws, bd, 0u);
     uint32_t w0[4];  // the top cell's current Philox block
     {
         const u32x4 r = philox4x32_10_lane(A.key0, A.key1, 0u, cell0, tile, A.c3);
@@ -400,7 +422,7 @@ __device__ __forceinline__ void sweep_db_rows(const StepArgs &A, uint32_t *smem,
             // the top cell's attempt of the next round, published for the column above
             uint32_t f16n = 0u, rbn = 0u;
             if (has_next) {
-                f16n = next_block_field(A, bd, rho + 1u, tile);
+                f16n = next_block_field(draws, bd, rho + 1u);
                 if (k == RPB - 1) {
                     const u32x4 r = philox4x32_10_lane(A.key0, A.key1, blk + 1u, cell0, tile, A.c3);
                     w0[0] = r.x; w0[1] = r.y; w0[2] = r.z; w0[3] = r.w;

@@ -423,6 +423,7 @@ __device__ __forceinline__ void sweep_dt_cells(const StepArgs &A, uint32_t *smem
     const uint32_t cell0 = G * S::CPT * NCX + cx;
     constexpr uint32_t RPB = MODE == kDraw ? 8u : 32u;  // rounds of one Philox block
     BlockDraw bd = {0u, 0u, 0u, 0u};
+    const u32x4 draws = block_draws(A, tile);
 #pragma unroll 1
     for (uint32_t blk = 0; blk < 64u / RPB; ++blk) {
         uint32_t rnd[NP][8];  // 16 bits of the pair's two cells each
@@ -459,7 +460,7 @@ __device__ __forceinline__ void sweep_dt_cells(const StepArgs &A, uint32_t *smem
 #pragma unroll 1
                 for (uint32_t n = 0; n < 4u; ++n) {
                     const uint32_t rho = (blk * 8u + r) * 4u + n;
-                    const uint32_t f16 = next_block_field(A, bd, rho, tile);
+                    const uint32_t f16 = next_block_field(draws, bd, rho);
 #pragma unroll
                     for (int j = 0; j < NP; ++j) {
                         site[j] = pk_bit(cur[j]);
@@ -469,7 +470,7 @@ __device__ __forceinline__ void sweep_dt_cells(const StepArgs &A, uint32_t *smem
                 }
             } else {
                 const uint32_t rho = blk * 8u + r;
-                const uint32_t f16 = next_block_field(A, bd, rho, tile);
+                const uint32_t f16 = next_block_field(draws, bd, rho);
                 const uint32_t pp = A.P_hi | A.P_hi << 16, qq = A.Q_hi | A.Q_hi << 16;
                 uint32_t tie = ~0u;
 #pragma unroll

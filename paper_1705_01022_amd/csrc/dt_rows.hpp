@@ -66,6 +66,7 @@ __device__ __forceinline__ void sweep_dt_rows(const StepArgs &A, uint32_t *smem,
     };
 
     BlockDraw bd = {0u, 0u, 0u, 0u};
+    const u32x4 draws = block_draws(A, tile);
     __syncthreads();
     const uint32_t nblk = A.rounds / RPB;
     for (uint32_t blk = 0; blk < nblk; ++blk) {
@@ -78,7 +79,7 @@ __device__ __forceinline__ void sweep_dt_rows(const StepArgs &A, uint32_t *smem,
 #pragma unroll
         for (int k = 0; k < RPB; ++k) {
             const uint32_t rho = blk * RPB + k;
-            const uint32_t f16 = next_block_field(A, bd, rho, tile);
+            const uint32_t f16 = next_block_field(draws, bd, rho);
             // the round's quadrant (and, DTr, the shift of the cell grid)
             uint32_t cu = base_u + ((f16 & 1u) << QL), cv = base_v0 + (((f16 >> 1) & 1u) << QL);
             if (SCHEME == kDTR) {

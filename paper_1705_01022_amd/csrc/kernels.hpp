@@ -255,6 +255,32 @@ __device__ __forceinline__ uint32_t next_block_field(const StepArgs &A, BlockDra
     return f16;
 }
 
+// The same fields for at most 64 rounds, from Philox blocks that eight lanes
+// work out at the start of a sweep: a refill is four lane reads instead of the
+// scalar unit's hundred instructions, which every wave waits for.
+__device__ __forceinline__ u32x4 block_draws(const StepArgs &A, uint32_t tile)
+{
+    return philox4x32_10_lane(A.key0, A.key1, threadIdx.x & 7u, 0xFFFFFFFFu, tile, A.c3);
+}
+
+__device__ __forceinline__ uint32_t next_block_field(const u32x4 &draws, BlockDraw &b, uint32_t rho)
+{
+    if ((rho & 7u) == 0u) {
+        const int l = (int)((rho >> 3) & 7u);
+        b.w0 = (uint32_t)__builtin_amdgcn_readlane((int)draws.x, l);
+        b.w1 = (uint32_t)__builtin_amdgcn_readlane((int)draws.y, l);
+        b.w2 = (uint32_t)__builtin_amdgcn_readlane((int)draws.z, l);
+        b.w3 = (uint32_t)__builtin_amdgcn_readlane((int)draws.w, l);
+    }
+    const uint32_t f16 = b.w0 & 0xFFFFu;
+    if (rho & 1u) {
+        b.w0 = b.w1; b.w1 = b.w2; b.w2 = b.w3;
+    } else {
+        b.w0 >>= 16;
+    }
+    return f16;
+}
+
 // Site of a cell's attempt from its field (low s_bits) and the round's block
 // field f16.  base_u, base_v: the cell's corner in the domain; offx, offy:
 // the domain's offset inside its first block / band.

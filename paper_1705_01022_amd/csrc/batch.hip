@@ -98,6 +98,21 @@ __device__ __forceinline__ u32x4 mcs_origin(const BatchSlot &S, uint64_t m, uint
     return w;
 }
 
+// The same in scalar registers: the compiler loads a table that the kernel's
+// own stores might change into one vector register per word otherwise, 38 of
+// them through the whole sweep (the four-cell DB sweep with draws spilled 53).
+__device__ __forceinline__ StepArgs uniform(const StepArgs &a)
+{
+    static_assert(sizeof(StepArgs) % 4 == 0, "whole words");
+    uint32_t w[sizeof(StepArgs) / 4];
+    __builtin_memcpy(w, &a, sizeof(a));
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(StepArgs) / 4; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[i]);
+    StepArgs r;
+    __builtin_memcpy(&r, w, sizeof(r));
+    return r;
+}
+
 // The items of one workgroup, in ticket order, until the queue is empty:
 // sweep(S, A, tile) is the device step of one tile of the lattice of slot S.
 // SHARED: the sweep reads and writes the lattice past the die-private caches by
@@ -205,7 +220,7 @@ __device__ __forceinline__ void batch_items(const BatchArgs &B, Sweep sweep)
         const uint32_t tile = __builtin_amdgcn_readfirstlane(cmd[1]);
         const uint32_t g = __builtin_amdgcn_readfirstlane(cmd[2]);
         const BatchSlot &S = B.slots[r];
-        StepArgs A = S.a;
+        StepArgs A = uniform(S.a);
         // MCS draw of the lattice's MCS m (as on the host): origin and set order
         const uint64_t m = B.mcs_base[r] + (g >> 2);
         const uint32_t k = g & 3u;
@@ -249,9 +264,7 @@ __device__ __forceinline__ void batch_items(const BatchArgs &B, Sweep sweep)
 // DT and DTr with at most 4 cells per lane: six waves per SIMD (80 VGPRs;
 // the generic sweep spills 40 bytes to scratch for it and ran faster than
 // with the five waves its unconstrained 93 VGPRs allow; the row-paired sweep
-// fits).  The row-paired DB sweep runs
-// two cells per lane (63 VGPRs): with four, the batch kernel's own state on
-// top of the sweep's needs 117 VGPRs (four waves), or spills at five.
+// fits), as do the row-paired sweeps.
 template <int SCHEME, int CPT, bool COLS, int FL, int LD>
 __global__ void __launch_bounds__(kMaxStepThreads)
 __attribute__((amdgpu_waves_per_eu((SCHEME != kDB && CPT <= 4) || LD > 0 ? 6 : 1)))
@@ -286,6 +299,16 @@ batch_kernel(BatchArgs B)
             else
                 sweep_tile<SCHEME, false, CPT, false>(A, smem, tile);
         }
+    });
+}
+
+// DB members with one cell per lane (db_cells.hpp), square 2^LD-site domains.
+template <bool ACCEPT, int LD>
+__global__ void __launch_bounds__(CellLaneShape<LD>::NT) batch_db_cells_kernel(BatchArgs B)
+{
+    extern __shared__ uint32_t smem[];
+    batch_items<true>(B, [&](const BatchSlot &, const StepArgs &A, uint32_t tile) {
+        sweep_db_cells<ACCEPT, LD, true>(A, smem, tile);
     });
 }
 
@@ -548,6 +571,8 @@ const void *batch_kernel_for(int scheme, uint32_t cpt, bool cols, int fl, int ld
         default: return nullptr;
         }
     }
+    if (cpt == 4 && ld == 8) return fl == 4 ? batch_fn<kDB, 4, true, 4, 8>() : batch_fn<kDB, 4, true, 3, 8>();
+    if (cpt == 4 && ld == 7) return fl == 4 ? batch_fn<kDB, 4, true, 4, 7>() : batch_fn<kDB, 4, true, 3, 7>();
     if (cpt == 2 && ld == 8) return fl == 4 ? batch_fn<kDB, 2, true, 4, 8>() : batch_fn<kDB, 2, true, 3, 8>();
     if (cpt == 2 && ld == 7) return fl == 4 ? batch_fn<kDB, 2, true, 4, 7>() : batch_fn<kDB, 2, true, 3, 7>();
 #define OKPZ_BATCH_CASES(S)                          \
@@ -760,7 +785,11 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
         int dev = 0, cus = 0;
         HIP_TRY(hipGetDevice(&dev));
         HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        const uint32_t cap = default_threads(tiles, (uint32_t)std::max(cus, 1), max_cells);
+        // the batch's DB step keeps the larger workgroup up to eight tiles per
+        // compute unit (1024 tiles of 1024 cells: 3.89 ms against 4.02 with
+        // 256 lanes; 4096 tiles: 256 lanes 11.1 ms against 14.4)
+        const uint64_t few = b->scheme == kDB ? (tiles + 1u) / 2u : tiles;
+        const uint32_t cap = default_threads(few, (uint32_t)std::max(cus, 1), max_cells);
         nt = 64;
         while (nt < cap && nt < max_cells) nt *= 2;
     }
@@ -834,19 +863,14 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
                 fl = 0;
     }
     // square 128- or 256-site domains of 8 x 8-site cells throughout: the
-    // row-paired sweep (its own LDS size), two cells per lane: four per lane
-    // take twice the lanes
+    // row-paired sweep (its own LDS size), two or four cells per lane
     int ld = 0;
-    if (fl > 0 && (cpt == 2 || (cpt == 4 && 2 * nt <= (uint32_t)kMaxStepThreads))) {
+    if (fl > 0 && (cpt == 2 || cpt == 4)) {
         const uint32_t d0 = slots[0].a.Dx;
         ld = d0 == 256u ? 8 : d0 == 128u ? 7 : 0;
         for (uint32_t i = 0; i < n && ld; ++i) {
             const StepArgs &a = slots[i].a;
             if (a.Dx != d0 || a.Dy != d0 || a.log2Cx != 3u || a.log2Cy != 3u || a.s_bits != 6u) ld = 0;
-        }
-        if (ld && cpt == 4) {
-            nt *= 2;
-            cpt = 2;
         }
         if (ld == 8) lds = 4u * rowpair_lds_words<8, 3>(nt);
         if (ld == 7) lds = 4u * rowpair_lds_words<7, 3>(nt);
@@ -867,6 +891,27 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
         }
     }
     const void *fn = batch_kernel_for(b->scheme, cpt, cols, fl, ld);
+    // few tiles of DB members that the row-paired sweep would serve: one cell per lane
+    if (ld && b->scheme == kDB) {
+        int dev = 0, cus = 0;
+        HIP_TRY(hipGetDevice(&dev));
+        HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        if (db_cells_few(slots[0].a.Dx, b->threads, prefix[n], (uint32_t)std::max(cus, 1))) {
+            const bool draws = fl == 4;
+            if (ld == 8) {
+                fn = draws ? reinterpret_cast<const void *>(&batch_db_cells_kernel<true, 8>)
+                           : reinterpret_cast<const void *>(&batch_db_cells_kernel<false, 8>);
+                nt = CellLaneShape<8>::NT;
+                lds = 4u * CellLaneShape<8>::LDS_WORDS;
+            } else {
+                fn = draws ? reinterpret_cast<const void *>(&batch_db_cells_kernel<true, 7>)
+                           : reinterpret_cast<const void *>(&batch_db_cells_kernel<false, 7>);
+                nt = CellLaneShape<7>::NT;
+                lds = 4u * CellLaneShape<7>::LDS_WORDS;
+            }
+            cpt = 1;
+        }
+    }
     // DT members that all hold their domains in registers
     bool regs = true, any128 = false, any256 = false;
     for (int32_t s : order) {

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "../../include/okpz.h"
+#include "db_cells.hpp"
 #include "db_rows.hpp"
 #include "dt_cells.hpp"
 #include "dt_rows.hpp"
@@ -264,11 +265,23 @@ inline void step_shape(uint32_t ncell, uint32_t threads, uint32_t &cpt, uint32_t
     }
 }
 
-// Domains the DT step holds in registers (dt_cells.hpp).
-inline bool dt_cells_shape(const okpz_params &p)
+// Domains of the kernels made for one shape: square, 128 or 256 sites, 8 x 8-site cells.
+inline bool square_cells(const okpz_params &p)
 {
-    return p.block_scheme == OKPZ_BLOCK_DT && p.device_layer == OKPZ_DEVICE_DT && p.dom_x == p.dom_y &&
-           (p.dom_x == 128u || p.dom_x == 256u) && p.cell_x == 8u && p.cell_y == 8u;
+    return p.device_layer == OKPZ_DEVICE_DT && p.dom_x == p.dom_y && (p.dom_x == 128u || p.dom_x == 256u) &&
+           p.cell_x == 8u && p.cell_y == 8u;
+}
+
+// Domains the DT step holds in registers (dt_cells.hpp).
+inline bool dt_cells_shape(const okpz_params &p) { return p.block_scheme == OKPZ_BLOCK_DT && square_cells(p); }
+
+// Domains the DB step may take with one cell per lane (db_cells.hpp), and whether it does.
+inline bool db_cells_shape(const okpz_params &p) { return p.block_scheme == OKPZ_BLOCK_DB && square_cells(p); }
+
+inline bool db_cells_few(uint32_t dom, uint32_t threads, uint64_t ntiles, uint32_t cus)
+{
+    if (threads) return dom == 128u && threads == 256u;
+    return ntiles <= (dom == 128u ? 4ull : 1ull) * cus;
 }
 
 // Waves per tile of that step: one for 128-site domains (two leave a lane one

@@ -127,6 +127,17 @@ int launch_dt_cells(const okpz_lattice *lat, uint32_t ntiles, const StepArgs &a,
     }
 }
 
+// DB with one cell per lane, on the same domains.
+int launch_db_cells(uint32_t ntiles, hipStream_t st, const StepArgs &a, bool accept)
+{
+    constexpr size_t l8 = 4u * CellLaneShape<8>::LDS_WORDS, l7 = 4u * CellLaneShape<7>::LDS_WORDS;
+    if (a.Dx == 256u)
+        return accept ? launch_instance(&step_db_cells_kernel<true, 8>, CellLaneShape<8>::NT, ntiles, l8, st, a)
+                      : launch_instance(&step_db_cells_kernel<false, 8>, CellLaneShape<8>::NT, ntiles, l8, st, a);
+    return accept ? launch_instance(&step_db_cells_kernel<true, 7>, CellLaneShape<7>::NT, ntiles, l7, st, a)
+                  : launch_instance(&step_db_cells_kernel<false, 7>, CellLaneShape<7>::NT, ntiles, l7, st, a);
+}
+
 // DB runs the row-paired kernel where it applies, else, with at least two
 // cells per lane and at most 64 cells per domain row, the column-mapped
 // kernel (same results, less bookkeeping than the generic one).
@@ -178,6 +189,12 @@ int launch_step(okpz_lattice *lat, const StepArgs &a, bool accept)
     const uint32_t ncell = a.ncell;
     const uint32_t span = a.dev_db ? 1u : 2u;  // dead border: every dom_x x dom_y tile in one step
     const uint32_t ntiles = (p.L / (span * p.dom_x)) * (p.L / (span * p.dom_y));
+    if (db_cells_shape(p) && db_cells_few(p.dom_x, lat->threads, ntiles, lat->cus)) {
+        const int rc = launch_db_cells(ntiles, lat->stream, a, accept);
+        if (rc != OKPZ_OK) return rc;
+        HIP_TRY(hipGetLastError());
+        return OKPZ_OK;
+    }
     if (dt_cells_shape(p)) {
         const int rc = launch_dt_cells(lat, ntiles, a, accept);
         if (rc != OKPZ_OK) return rc;

@@ -66,8 +66,7 @@ struct okpz_lattice {
     int32_t *h0s = nullptr;
     uint32_t *snap = nullptr;
     int64_t *partial = nullptr;
-    int64_t *reduced = nullptr;
-    int64_t *host_out = nullptr;  // pinned
+    int64_t *host_out = nullptr;  // pinned; the measurement's last kernel writes it
     bool has_snap = false;
     uint64_t snap_mcs = 0;
     __int128 snap_s1 = 0;

@@ -230,7 +230,7 @@ int fill_flat(okpz_lattice *lat)
 }
 
 // Heights of the current words into h0 (anchors) and per-row partials, then
-// the exact totals into lat->host_out (10 or 5x2 int64).  cross: also sum
+// the exact totals into lat->host_out (six 128-bit pairs).  cross: also sum
 // h_t h_s against the snapshot.
 int run_measure(okpz_lattice *lat, bool cross, const uint32_t *src, int32_t *h0_dst)
 {
@@ -250,11 +250,12 @@ int run_measure(okpz_lattice *lat, bool cross, const uint32_t *src, int32_t *h0_
     else
         hipLaunchKernelGGL((rows_kernel<false>), dim3(blocks), dim3(kMeasureThreads), 0, lat->stream, src, h0_dst,
                            nullptr, nullptr, p.L, nbx_log2, lat->partial);
-    hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kReduceThreads), 0, lat->stream, lat->partial, p.L / 4, lat->reduced);
+    // the totals go straight to the pinned host buffer: a copy after the kernel
+    // is another packet in the queue (L = 2048: 30.7 -> 29.8 us a measurement)
+    hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kReduceThreads), 0, lat->stream, lat->partial, p.L / 4,
+                       lat->host_out);
     end_timed(lat, tp);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(lat->host_out, lat->reduced, 2 * kMomentFields * sizeof(int64_t),
-                           hipMemcpyDeviceToHost, lat->stream));
     HIP_TRY(hipStreamSynchronize(lat->stream));
     return OKPZ_OK;
 }
@@ -407,7 +408,6 @@ void release(okpz_lattice *lat)
     if (lat->h0s) (void)hipFree(lat->h0s);
     if (lat->snap) (void)hipFree(lat->snap);
     if (lat->partial) (void)hipFree(lat->partial);
-    if (lat->reduced) (void)hipFree(lat->reduced);
     if (lat->host_out) (void)hipHostFree(lat->host_out);
     delete lat;
 }
@@ -440,7 +440,6 @@ int create_common(const okpz_params *params, void *hip_stream, void *dev_words, 
     const uint32_t L = params->L;
     if (hipMalloc(&lat->h0, L * sizeof(int32_t)) != hipSuccess ||
         hipMalloc(&lat->partial, (size_t)(L / 4) * kMomentFields * sizeof(int64_t)) != hipSuccess ||
-        hipMalloc(&lat->reduced, 2 * kMomentFields * sizeof(int64_t)) != hipSuccess ||
         hipHostMalloc(&lat->host_out, 2 * kMomentFields * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
         release(lat);
         return OKPZ_ENOMEM;

@@ -32,6 +32,7 @@
 #include <new>
 
 #include "internal.hpp"
+#include "mcs_draw.hpp"
 #include "neighbourhood.hpp"
 
 using namespace okpz;
@@ -68,37 +69,12 @@ struct BatchArgs {
     uint64_t wait_ticks;  // wait limit in wall-clock ticks
 };
 
-// Element k of permutation number `pick` (lexicographic order) of {0,1,2,3}.
-__device__ __forceinline__ uint32_t perm_element(uint32_t pick, uint32_t k)
-{
-    uint32_t avail = 0x3210u;  // remaining elements, 4 bits each, ascending
-    const uint32_t digit[4] = {pick / 6u, (pick % 6u) / 2u, pick % 2u, 0u};
-    uint32_t e = 0;
-    for (uint32_t i = 0; i <= k; ++i) {
-        const uint32_t sh = 4u * digit[i];
-        e = (avail >> sh) & 0xFu;
-        const uint32_t low = avail & ((1u << sh) - 1u);
-        avail = low | ((avail >> (sh + 4u)) << sh);
-    }
-    return e;
-}
-
-// Tiling origin of MCS m of a lattice (as the host draws it) and the word w
-// whose third element picks the order of the domain sets.
 __device__ __forceinline__ u32x4 mcs_origin(const BatchSlot &S, uint64_t m, uint32_t &ox, uint32_t &oy)
 {
-    const u32x4 w = philox4x32_10(S.a.key0, S.a.key1, 0u, 0xFFFFFFFFu, 0xFFFFFFFFu, (uint32_t)(m << 2));
-    ox = w.x & S.a.L_mask;
-    oy = w.y & S.a.L_mask;
-    if (S.origin_mode == OKPZ_ORIGIN_FIXED) ox = oy = 0u;
-    if (S.origin_mode == OKPZ_ORIGIN_COARSE) {
-        ox &= ~3u;
-        oy &= ~3u;
-    }
-    return w;
+    return okpz::mcs_origin(S.a, (int32_t)S.origin_mode, m, ox, oy);
 }
 
-// The same in scalar registers: the compiler loads a table that the kernel's
+// Step arguments in scalar registers: the compiler loads a table that the kernel's
 // own stores might change into one vector register per word otherwise, 38 of
 // them through the whole sweep (the four-cell DB sweep with draws spilled 53).
 __device__ __forceinline__ StepArgs uniform(const StepArgs &a)

@@ -18,6 +18,7 @@
 #include "dt_rows.hpp"
 #include "kernels.hpp"
 #include "philox.hpp"
+#include "small_lattice.hpp"
 
 namespace okpz_host {
 

@@ -207,6 +207,7 @@ struct Draw {
                     // deposits, kFlipMax iff a local maximum is removed
     uint32_t pos;   // domain-local u | v << 16
     uint32_t rim;   // bit 0: right column of its cell, bit 1: bottom row (DB)
+    uint32_t u, v;  // domain-local site
 };
 
 // Consumes the next F-bit field of a cell's lane-draw stream for round rho
@@ -322,6 +323,8 @@ __device__ __forceinline__ Draw decode(const StepArgs &A, uint32_t field, uint32
     d.mask = ACCEPT ? field >> A.s_bits : A.flip_table;  // acceptance prefix until accept_draws()
     if (A.dev_db && (u == A.Dx - 1u || v == A.Dy - 1u))
         d.mask = ACCEPT ? 0xFFFFFFFFu : 0u;  // dead border: a prefix no threshold accepts
+    d.u = u;
+    d.v = v;
     d.pos = SCHEME == kDB ? u | (v << 16) : 0u;
     d.rim = SCHEME == kDB ? ((du == (1u << A.log2Cx) - 1u) ? 1u : 0u) | ((dv == (1u << A.log2Cy) - 1u) ? 2u : 0u)
                           : 0u;

@@ -351,7 +351,7 @@ struct MeasureSlot {
 
 __global__ void __launch_bounds__(1024) batch_anchors_kernel(const MeasureSlot *ms)
 {
-    __shared__ int32_t part[1024];
+    __shared__ int32_t part[16];
     const MeasureSlot &m = ms[blockIdx.x];
     anchors_body(m.src, m.L, m.nbx_log2, m.h0, part);
 }

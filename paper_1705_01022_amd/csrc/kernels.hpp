@@ -1005,10 +1005,27 @@ __device__ __forceinline__ uint32_t col0_bits(const uint32_t *__restrict__ words
     return (sy.x & 1u) | (sy.y & 1u) << 1 | (sy.z & 1u) << 2 | (sy.w & 1u) << 3;
 }
 
+// Exclusive prefix sum over the 64 lanes of a wave and the wave's total, by
+// data-parallel-primitive moves: shifts by 1, 2, 4, 8 within rows of 16
+// lanes (lanes shifted in from outside the row read 0), then the last lane of
+// row 0 into rows 1 and 3 and the last lane of row 1 into rows 2 and 3.
+__device__ __forceinline__ int32_t wave_excl_scan_i32(int32_t v, int32_t &total)
+{
+    int32_t inc = v;
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xF, 0xF, true);  // row_shr:1
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xF, 0xF, true);  // row_shr:2
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xF, 0xF, true);  // row_shr:4
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x118, 0xF, 0xF, true);  // row_shr:8
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1, 3
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2, 3
+    total = __builtin_amdgcn_readlane(inc, 63);
+    return inc - v;
+}
+
 // Column-0 anchors h(0,y) in one workgroup: each thread owns a run of up to 32
 // consecutive bands (L <= 2^17 with 1024 threads) whose column-0 bits it
 // holds in registers (bit 4k + r: row r of the run's band k, from `fetch(b)`,
-// eight fetches in flight at a time); a block scan joins the runs and each
+// eight fetches in flight at a time); wave scans and the waves' totals join the runs and each
 // thread writes its rows' heights, four at a time.
 template <typename Fetch>
 __device__ __forceinline__ void anchors_scan(Fetch fetch, uint32_t L, int32_t *__restrict__ h0, int32_t *part)
@@ -1034,15 +1051,12 @@ __device__ __forceinline__ void anchors_scan(Fetch fetch, uint32_t L, int32_t *_
     int32_t local = 2 * (int32_t)(__popc(bits[0]) + __popc(bits[1]) + __popc(bits[2]) + __popc(bits[3])) -
                     4 * (int32_t)nb;
     if (b0 == 0u && nb > 0u) local -= 2 * (int32_t)(bits[0] & 1u) - 1;
-    part[tid] = local;
+    // exclusive prefix h(0, 4 b0 - 1): within the wave, then the earlier waves' totals
+    int32_t total;
+    int32_t h = wave_excl_scan_i32(local, total);
+    if ((tid & 63u) == 0u) part[tid >> 6] = total;
     __syncthreads();
-    for (uint32_t off = 1; off < T; off <<= 1) {  // inclusive Hillis-Steele scan
-        const int32_t v = tid >= off ? part[tid - off] : 0;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
-    }
-    int32_t h = part[tid] - local;  // exclusive prefix: h(0, 4 b0 - 1)
+    for (uint32_t w = 0; w < tid >> 6; ++w) h += part[w];
 #pragma unroll
     for (uint32_t g = 0; g < 4; ++g) {
         if (8u * g >= nb) break;
@@ -1070,7 +1084,7 @@ __device__ __forceinline__ void anchors_body(const uint32_t *__restrict__ words,
     anchors_scan([&](uint32_t b) { return col0_bits(words, nbx_log2, b); }, L, h0, part);
 }
 
-// A single lattice in two launches: the column-0 bits of every band, one
+// A large lattice in two launches: the column-0 bits of every band, one
 // lane per band across the whole device (one 16-byte read per band, L/4 of
 // them 32 L bytes apart: spread over many compute units rather than queued in
 // one), one byte per band into col0; then the scan, in one workgroup, over
@@ -1085,25 +1099,34 @@ static __global__ void __launch_bounds__(256) col0_kernel(const uint32_t *__rest
 static __global__ void __launch_bounds__(1024) anchors_kernel(const uint8_t *__restrict__ col0, uint32_t L,
                                                               int32_t *__restrict__ h0)
 {
-    __shared__ int32_t part[1024];
+    __shared__ int32_t part[16];
     anchors_scan([&](uint32_t b) { return (uint32_t)col0[b]; }, L, h0, part);
 }
 
-// Exclusive prefix sum over the 64 lanes of a wave and the wave's total, by
-// data-parallel-primitive moves: shifts by 1, 2, 4, 8 within rows of 16
-// lanes (lanes shifted in from outside the row read 0), then the last lane of
-// row 0 into rows 1 and 3 and the last lane of row 1 into rows 2 and 3.
-__device__ __forceinline__ int32_t wave_excl_scan_i32(int32_t v, int32_t &total)
+// A lattice of at most one band per lane (1024 of them) in one launch of L / 4
+// lanes, 64 at least.  A measurement of a small lattice is launches and their
+// chains of latency: 30.4 us at L = 512 before, 22.5 with this launch in place
+// of two, the scan by wave moves (it was ten barriered steps over LDS) and the
+// reduction by as many waves as its rows need.
+constexpr uint32_t kAnchorsDirectL = 4096;
+
+static __global__ void __launch_bounds__(1024) anchors_direct_kernel(const uint32_t *__restrict__ words, uint32_t L,
+                                                                     uint32_t nbx_log2, int32_t *__restrict__ h0)
 {
-    int32_t inc = v;
-    inc += __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xF, 0xF, true);  // row_shr:1
-    inc += __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xF, 0xF, true);  // row_shr:2
-    inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xF, 0xF, true);  // row_shr:4
-    inc += __builtin_amdgcn_update_dpp(0, inc, 0x118, 0xF, 0xF, true);  // row_shr:8
-    inc += __builtin_amdgcn_update_dpp(0, inc, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1, 3
-    inc += __builtin_amdgcn_update_dpp(0, inc, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2, 3
-    total = __builtin_amdgcn_readlane(inc, 63);
-    return inc - v;
+    __shared__ int32_t part[16];
+    anchors_body(words, L, nbx_log2, h0, part);
+}
+
+// Anchors of a single lattice; col0: L / 4 bytes of scratch.
+inline void launch_anchors(const uint32_t *words, uint32_t L, uint32_t nbx_log2, uint8_t *col0, int32_t *h0,
+                           hipStream_t stream)
+{
+    if (L <= kAnchorsDirectL) {
+        hipLaunchKernelGGL(anchors_direct_kernel, dim3(1), dim3(L / 4 > 64u ? L / 4 : 64u), 0, stream, words, L, nbx_log2, h0);
+        return;
+    }
+    hipLaunchKernelGGL(col0_kernel, dim3((L / 4 + 255) / 256), dim3(256), 0, stream, words, L, nbx_log2, col0);
+    hipLaunchKernelGGL(anchors_kernel, dim3(1), dim3(1024), 0, stream, col0, L, h0);
 }
 
 __device__ __forceinline__ int64_t wave_sum_i64(int64_t v)
@@ -1443,6 +1466,14 @@ static __global__ void __launch_bounds__(kReduceThreads) reduce_kernel(const int
     __shared__ uint64_t lo_s[kMomentFields][kReduceMaxWaves];
     __shared__ int64_t hi_s[kMomentFields][kReduceMaxWaves];
     reduce_body(partial, nrows, out, lo_s, hi_s);
+}
+
+// Lanes of the reduction of a lattice's L / 4 rows: four rows each, the loads
+// it has in flight at a time; more waves only queue for the shuffles.
+inline uint32_t reduce_threads(uint32_t L)
+{
+    const uint32_t t = L / 16u;
+    return t < 64u ? 64u : t > (uint32_t)kReduceThreads ? (uint32_t)kReduceThreads : t;
 }
 
 }  // namespace okpz

@@ -1,7 +1,7 @@
 """Small lattices: whole MCS in one launch (L <= 128, 8 x 8 cells) against the
 oracle's DTr emulation, for every scheme, one to sixteen tiles, square and
 oblong domains, each origin mode and runs split at odd places; and the
-measurement, whose totals the last kernel writes to host memory."""
+measurement with one lane a band (up to L = 4096)."""
 import numpy as np
 import pytest
 
@@ -46,7 +46,7 @@ def test_origin_modes_and_launch_limit(okpz, orc, origin, scheme):
         assert np.array_equal(lat.sites(), ref)
 
 
-@pytest.mark.parametrize("L", [64, 128, 256, 512, 1024])
+@pytest.mark.parametrize("L", [64, 128, 256, 512, 1024, 4096])
 def test_measurement(okpz, orc, L):
     e = orc.Emu(L=L, Dx=16, Dy=16, Cx=8, Cy=8, scheme=orc.DT, p=0.9, q=0.1, seed=3, stream=2)
     ref = orc.init_flat(L)

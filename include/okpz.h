@@ -316,7 +316,12 @@ int okpz_get_mcs(const okpz_lattice *lat, uint64_t *mcs);
  * compute unit, else 256; at most ncell / 2 when the domain has 256 thread
  * cells or more, so that each thread holds two or more).  Each thread then
  * updates ncell / threads thread
- * cells (at most 16, else OKPZ_EINVAL).  A physical mapping only: the simulated
+ * cells (at most 16, else OKPZ_EINVAL).  Kernels made for a shape set their
+ * own: DT on square 128- or 256-site domains of 8 x 8-site cells runs one
+ * wave a tile (D = 128), two (D = 256, threads of 64 or 128, or 0 with many
+ * tiles) or four; DB on the same domains, with 0 and few tiles (D = 128: also
+ * 256), one cell per thread; and with 0 lattices of L <= 128 with such cells
+ * run whole MCS in one launch of one wave.  A physical mapping only: the simulated
  * lattice does not depend on it (every random draw is keyed by cell, not by
  * thread).  Chosen by an autotuner per domain shape.
  */
@@ -330,8 +335,9 @@ int okpz_sync(okpz_lattice *lat);
 
 /*
  * Per-kernel timing with HIP events recorded on the handle's stream around
- * every launch of the device-step kernel (four per MCS) and of the
- * measurement kernels.  okpz_timing(lat, 1) enables and zeroes the
+ * every launch of the device-step kernel (four per MCS, also where small
+ * lattices otherwise run whole MCS in one launch) and of the measurement
+ * kernels.  okpz_timing(lat, 1) enables and zeroes the
  * counters; okpz_timing(lat, 0) disables.  okpz_get_timing synchronises and
  * returns total milliseconds and launch counts.
  */
@@ -394,7 +400,8 @@ int okpz_batch_size(const okpz_batch *batch, uint32_t *nslots);
  * threads per workgroup (64, 128, 256, 512, or 0: enough lanes for the
  * largest domain's cells, at most 256, or 512 when the launch has fewer
  * tiles per step than four per compute unit, and at most half the cells of
- * a domain of 256 cells or more), persistent workgroups
+ * a domain of 256 cells or more; the kernels made for a shape set their own
+ * as for okpz_set_threads), persistent workgroups
  * (0 = as many as fit on the device at once, but no more than the members'
  * tiles in one step), use_graph (capture and replay the launch).  Chosen by
  * the autotuner of the Python layer.

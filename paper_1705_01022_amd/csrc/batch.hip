@@ -251,14 +251,14 @@ batch_kernel(BatchArgs B)
         if constexpr (LD > 0 && SCHEME != kDB) {
             if (A.Dx == 256u) {
                 if (S.accept)
-                    sweep_dt_rows<SCHEME, true, CPT, 8, 3, true>(A, smem, tile);
+                    sweep_dt_rows<true, CPT, 8, 3, true>(A, smem, tile);
                 else
-                    sweep_dt_rows<SCHEME, false, CPT, 8, 3, true>(A, smem, tile);
+                    sweep_dt_rows<false, CPT, 8, 3, true>(A, smem, tile);
             } else {
                 if (S.accept)
-                    sweep_dt_rows<SCHEME, true, CPT, 7, 3, true>(A, smem, tile);
+                    sweep_dt_rows<true, CPT, 7, 3, true>(A, smem, tile);
                 else
-                    sweep_dt_rows<SCHEME, false, CPT, 7, 3, true>(A, smem, tile);
+                    sweep_dt_rows<false, CPT, 7, 3, true>(A, smem, tile);
             }
         } else if constexpr (LD > 0) {
             sweep_db_rows<FL == 4, CPT, LD, 3, true>(A, smem, tile);

@@ -91,12 +91,12 @@ bool launch_dtr_rows(uint32_t nt, uint32_t ntiles, hipStream_t st, const StepArg
             a.shared_edges)
             return false;
         if (a.Dx == 256u) {
-            rc = launch_instance(&step_dt_rows_kernel<kDTR, ACCEPT, CPT, 8, 3>, nt, ntiles,
+            rc = launch_instance(&step_dt_rows_kernel<ACCEPT, CPT, 8, 3>, nt, ntiles,
                                  4u * rowpair_dt_lds_words<8, 3>(), st, a);
             return true;
         }
         if (a.Dx == 128u) {
-            rc = launch_instance(&step_dt_rows_kernel<kDTR, ACCEPT, CPT, 7, 3>, nt, ntiles,
+            rc = launch_instance(&step_dt_rows_kernel<ACCEPT, CPT, 7, 3>, nt, ntiles,
                                  4u * rowpair_dt_lds_words<7, 3>(), st, a);
             return true;
         }

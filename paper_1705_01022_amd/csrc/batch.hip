@@ -77,6 +77,9 @@ __device__ __forceinline__ u32x4 mcs_origin(const BatchSlot &S, uint64_t m, uint
 // Step arguments in scalar registers: the compiler loads a table that the kernel's
 // own stores might change into one vector register per word otherwise, 38 of
 // them through the whole sweep (the four-cell DB sweep with draws spilled 53).
+// For the sweeps made for a shape, which use few of them; the generic sweeps
+// use most of them in vector instructions, of which each takes one scalar, and
+// ran 2-4 % slower so (DT, D = 128, 16 x 16 cells).
 __device__ __forceinline__ StepArgs uniform(const StepArgs &a)
 {
     static_assert(sizeof(StepArgs) % 4 == 0, "whole words");
@@ -196,7 +199,7 @@ __device__ __forceinline__ void batch_items(const BatchArgs &B, Sweep sweep)
         const uint32_t tile = __builtin_amdgcn_readfirstlane(cmd[1]);
         const uint32_t g = __builtin_amdgcn_readfirstlane(cmd[2]);
         const BatchSlot &S = B.slots[r];
-        StepArgs A = uniform(S.a);
+        StepArgs A = SHARED ? uniform(S.a) : S.a;
         // MCS draw of the lattice's MCS m (as on the host): origin and set order
         const uint64_t m = B.mcs_base[r] + (g >> 2);
         const uint32_t k = g & 3u;

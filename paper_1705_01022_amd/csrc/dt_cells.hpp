@@ -27,9 +27,9 @@
 // The step is bound by vector issue: 90 % VALU busy at p = 1 (95 % with
 // draws), where the row-paired LDS kernel it replaces was bound by LDS and
 // issue together (73 % and 69 %).  D = 256, L = 2^16, per launch: p = 1 0.863
-// -> 0.435 ms (28.6 -> 14.3 VALU instructions per wave-attempt), p = 0.95
-// 0.94 -> 0.72 ms; D = 128 p = 1 0.90 -> 0.47 ms, p = 1/2 0.96 -> 0.65 ms; 64
-// tiles (L = 4096) 31.1 -> 25 us.  Two waves per tile rather than one (which
+// -> 0.41 ms (28.6 -> 14.3 VALU instructions per wave-attempt), p = 0.95
+// 0.94 -> 0.68 ms; D = 128 p = 1 0.90 -> 0.47 ms, p = 1/2 0.96 -> 0.65 ms; 64
+// tiles (L = 4096) 31.1 -> 22.4 us.  Two waves per tile rather than one (which
 // needs no barrier and fewer instructions): a single wave holds 16 cells a
 // lane, 168 registers with spills, three waves per SIMD, 66-77 % VALU busy and
 // 0.51 ms (0.97 with draws).

@@ -274,7 +274,7 @@ batch_kernel(BatchArgs B)
                 sweep_db_columns<false, CPT, 0>(A, smem, tile);
         } else {
             if (S.accept)
-                sweep_tile<SCHEME, true, CPT, false>(A, smem, tile);
+                sweep_tile<SCHEME, true, CPT, false, SCHEME != kDB && CPT == 1>(A, smem, tile);
             else
                 sweep_tile<SCHEME, false, CPT, false>(A, smem, tile);
         }

@@ -207,7 +207,6 @@ struct Draw {
                     // deposits, kFlipMax iff a local maximum is removed
     uint32_t pos;   // domain-local u | v << 16
     uint32_t rim;   // bit 0: right column of its cell, bit 1: bottom row (DB)
-    uint32_t u, v;  // domain-local site
 };
 
 // Consumes the next F-bit field of a cell's lane-draw stream for round rho
@@ -284,14 +283,13 @@ __device__ __forceinline__ uint32_t next_block_field(const u32x4 &draws, BlockDr
 }
 
 // Site of a cell's attempt from its field (low s_bits) and the round's block
-// field f16.  base_u, base_v: the cell's corner in the domain; offx, offy:
-// the domain's offset inside its first block / band.
-template <int SCHEME, bool ACCEPT>
-__device__ __forceinline__ Draw decode(const StepArgs &A, uint32_t field, uint32_t f16, uint32_t base_u,
-                                       uint32_t base_v, uint32_t offx, uint32_t offy)
+// field f16: in its cell (du, dv) and in the domain (u, v).  base_u, base_v:
+// the cell's corner in the domain.
+template <int SCHEME>
+__device__ __forceinline__ void drawn_site(const StepArgs &A, uint32_t field, uint32_t f16, uint32_t base_u,
+                                           uint32_t base_v, uint32_t &du, uint32_t &dv, uint32_t &u, uint32_t &v)
 {
     const uint32_t idx = field & ((1u << A.s_bits) - 1u);
-    uint32_t du, dv, u, v;
     if (SCHEME == kDB) {
         du = idx & ((1u << A.log2Cx) - 1u);
         dv = idx >> A.log2Cx;
@@ -308,6 +306,16 @@ __device__ __forceinline__ Draw decode(const StepArgs &A, uint32_t field, uint32
         u = (shx + base_u + du) & (A.Dx - 1u);
         v = (shy + base_v + dv) & (A.Dy - 1u);
     }
+}
+
+// The attempt's addresses, mask and rim.  offx, offy: the domain's offset
+// inside its first block / band.
+template <int SCHEME, bool ACCEPT>
+__device__ __forceinline__ Draw decode(const StepArgs &A, uint32_t field, uint32_t f16, uint32_t base_u,
+                                       uint32_t base_v, uint32_t offx, uint32_t offy)
+{
+    uint32_t du, dv, u, v;
+    drawn_site<SCHEME>(A, field, f16, base_u, base_v, du, dv, u, v);
     const uint32_t lx = u + offx, ly = v + offy;
     Draw d;
     if (SCHEME == kDB) {
@@ -324,8 +332,6 @@ __device__ __forceinline__ Draw decode(const StepArgs &A, uint32_t field, uint32
     d.mask = ACCEPT ? field >> A.s_bits : A.flip_table;  // acceptance prefix until accept_draws()
     if (A.dev_db && (u == A.Dx - 1u || v == A.Dy - 1u))
         d.mask = ACCEPT ? 0xFFFFFFFFu : 0u;  // dead border: a prefix no threshold accepts
-    d.u = u;
-    d.v = v;
     d.pos = SCHEME == kDB ? u | (v << 16) : 0u;
     d.rim = SCHEME == kDB ? ((du == (1u << A.log2Cx) - 1u) ? 1u : 0u) | ((dv == (1u << A.log2Cy) - 1u) ? 2u : 0u)
                           : 0u;
@@ -610,7 +616,20 @@ __host__ __device__ inline uint32_t step_lds_words(uint32_t NR, uint32_t P, uint
 // result equals bulk -> edges -> corners exactly.  Attempt sites depend only
 // on the random stream, so each cell publishes its next round's site one
 // round ahead (double-buffered in LDS) and the check needs no extra barrier.
-template <int SCHEME, bool ACCEPT, int CPT, bool FULL>
+//
+// LANES (DT, DTr): the block draws of 512 rounds are worked out by the wave's
+// lanes at a time, else each block by the scalar unit when its turn comes.  The
+// lanes' four words stay live through the sweep and the vector unit works out
+// 64 blocks where 8 x 8-site cells use eight, so single lattices, whose scalar
+// unit has room, lose by it (L = 1024, D = 16, p = 1: 97.6 us an MCS against
+// 102.5; L = 8192, D = 128, 16 x 16 cells, draws: 497 against 519), and so do
+// the batch's sweeps with four cells per lane or more (1600 tiles of D = 512:
+// 5.36 ms an MCS against 5.41, with 16 x 16 cells 5.57 against 5.68).  The
+// batch spills scalar registers, fewer of them so; with one cell per lane and draws it gains:
+// 64 realisations of L = 1024, D = 64, 16 x 16 cells 1036 us by the scalar unit,
+// 994 by the lanes; D = 128, 16 x 16 cells 653 and 643; D = 64, 8 x 8 cells,
+// L = 512 218.4 and 215.6; without draws D = 64 DTr 209.5 and 210.5.
+template <int SCHEME, bool ACCEPT, int CPT, bool FULL, bool LANES = false>
 __device__ __forceinline__ void sweep_tile(const StepArgs &A, uint32_t *smem, uint32_t tile)
 {
     const uint32_t tid = threadIdx.x, NT = blockDim.x;
@@ -658,11 +677,9 @@ __device__ __forceinline__ void sweep_tile(const StepArgs &A, uint32_t *smem, ui
         __syncthreads();
         u32x4 draws;
         for (uint32_t rho = 0; rho < A.rounds; ++rho) {
-            // the block draws of 512 rounds by the wave's lanes at a time (batches of
-            // DT lattices with 16 x 16-site cells: 11.80 -> 11.51 ms, 30.7 -> 29.8)
-            if ((rho & 511u) == 0u)
+            if (LANES && (rho & 511u) == 0u)
                 draws = philox4x32_10_lane(A.key0, A.key1, (rho >> 3) + (tid & 63u), 0xFFFFFFFFu, tile, A.c3);
-            const uint32_t f16 = next_block_field<64u>(draws, bd, rho);
+            const uint32_t f16 = LANES ? next_block_field<64u>(draws, bd, rho) : next_block_field(A, bd, rho, tile);
             Draw d[CPT];
 #pragma unroll
             for (int j = 0; j < CPT; ++j) {

@@ -84,11 +84,12 @@ __global__ void __launch_bounds__(64) run_small_kernel(StepArgs A, uint64_t mcs0
                 if ((rho & 1u) == 0u) fw = tile_fields[rho >> 1];
                 const uint32_t f16 = (rho & 1u) ? fw >> 16 : fw & 0xFFFFu;
                 const uint32_t field = next_field(A, rw, rho, cell, tile);
-                const Draw d = decode<SCHEME, ACCEPT>(A, field, f16, base_u, base_v, 0u, 0u);
-                s = (((Y0 + d.v) & A.L_mask) << log2L) + ((X0 + d.u) & A.L_mask);
-                pos = d.pos;
-                rim = d.rim;
-                uint32_t pre[1] = {d.mask};
+                uint32_t du, dv, u, v;
+                drawn_site<SCHEME>(A, field, f16, base_u, base_v, du, dv, u, v);
+                s = (((Y0 + v) & A.L_mask) << log2L) + ((X0 + u) & A.L_mask);
+                pos = SCHEME == kDB ? u | (v << 16) : 0u;
+                rim = SCHEME == kDB ? (du == 7u ? 1u : 0u) | (dv == 7u ? 2u : 0u) : 0u;
+                uint32_t pre[1] = {ACCEPT ? field >> A.s_bits : A.flip_table};  // prefix until accept_draws()
                 if (ACCEPT) {
                     const uint32_t ids[1] = {cell};
                     accept_draws<1>(A, pre, ids, rho, tile);

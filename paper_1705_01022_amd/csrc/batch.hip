@@ -71,7 +71,7 @@ struct BatchArgs {
 
 __device__ __forceinline__ u32x4 mcs_origin(const BatchSlot &S, uint64_t m, uint32_t &ox, uint32_t &oy)
 {
-    return okpz::mcs_origin(S.a, (int32_t)S.origin_mode, m, ox, oy);
+    return okpz::mcs_origin(S.a, S.origin_mode, m, ox, oy);
 }
 
 // Step arguments in scalar registers: the compiler loads a table that the kernel's
@@ -92,13 +92,77 @@ __device__ __forceinline__ StepArgs uniform(const StepArgs &a)
     return r;
 }
 
-// The items of one workgroup, in ticket order, until the queue is empty:
-// sweep(S, A, tile) is the device step of one tile of the lattice of slot S.
-// SHARED: the sweep reads and writes the lattice past the die-private caches by
-// itself, so items need no cache invalidation and no write-back.
-template <bool SHARED, typename Sweep>
-__device__ __forceinline__ void batch_items(const BatchArgs &B, Sweep sweep)
+// COLS: every lattice of the launch is DB with lanes x CPT cells per domain
+// and at most 64 cells per row, so the column-mapped sweep serves them all.
+// FL > 0 (with COLS): every lattice also draws 2^FL-bit lane fields, with
+// acceptance draws iff FL = 4 and a whole number of Philox blocks of rounds,
+// so the sweep with the rounds of one block unrolled serves them all.
+//
+// LD > 0 (with COLS and FL > 0): every lattice also has square 2^LD-site
+// domains of 8 x 8-site cells, so the row-paired DB sweep serves them all, or,
+// with CPT = 1, the one with a cell per lane (db_cells.hpp).
+// LD > 0 with DTr: every lattice has square 128- or 256-site domains of
+// 8 x 8-site cells, and each item runs the row-paired DTr sweep for its
+// lattice's domain size and rates.
+//
+// DT and DTr with at most 4 cells per lane: six waves per SIMD (80 VGPRs;
+// the generic sweep spills 40 bytes to scratch for it and ran faster than
+// with the five waves its unconstrained 93 VGPRs allow; the row-paired sweep
+// fits), as do the row-paired sweeps.
+//
+// NW > 0: DT members that all hold their domains in registers (dt_cells.hpp),
+// NW waves per workgroup: 128-site domains for one or two, 256-site ones for
+// two or four.
+//
+// SHARED (the sweeps made for a shape): the sweep reads and writes the lattice
+// past the die-private caches by itself, so items need no cache invalidation
+// and no write-back.
+//
+// The loop over the items and the sweeps stand in one body: with the sweep
+// handed to a common loop as a function object the compiler simplified it
+// before inlining it, and the generic sweeps with one cell per lane ran 1-3 %
+// slower (DB, 16 x 16-site cells, 90 realisations of L = 1024: 889 -> 906 us an MCS).
+template <int SCHEME, int CPT, bool COLS, int FL, int LD, int NW>
+constexpr int batch_threads()
 {
+    if constexpr (NW > 0)
+        return 64 * NW;
+    else if constexpr (SCHEME == kDB && LD > 0 && CPT == 1)
+        return (int)CellLaneShape<LD>::NT;
+    else
+        return kMaxStepThreads;
+}
+
+template <int SCHEME, int CPT, bool COLS, int FL, int LD, int NW>
+constexpr int batch_waves()
+{
+    if constexpr (NW > 0)
+        return NW == 2 ? 4 : 6;
+    else if constexpr (SCHEME == kDB && LD > 0 && CPT == 1)
+        return 1;
+    else
+        return (SCHEME != kDB && CPT <= 4) || LD > 0 ? 6 : 1;
+}
+
+// DT, the domain in registers, by how the lattice's rounds decide.
+template <int LD, int NW>
+__device__ __forceinline__ void batch_dt_cells(const StepArgs &A, uint32_t *smem, uint32_t tile, bool draws)
+{
+    if (draws)
+        sweep_dt_cells<kDraw, LD, NW, true>(A, smem, tile);
+    else if (A.flip_table == kFlipMin)
+        sweep_dt_cells<kDeposit, LD, NW, true>(A, smem, tile);
+    else
+        sweep_dt_cells<kSure, LD, NW, true>(A, smem, tile);
+}
+
+template <int SCHEME, int CPT, bool COLS, int FL, int LD, int NW = 0>
+__global__ void __launch_bounds__((batch_threads<SCHEME, CPT, COLS, FL, LD, NW>()))
+__attribute__((amdgpu_waves_per_eu((batch_waves<SCHEME, CPT, COLS, FL, LD, NW>()))))
+batch_kernel(BatchArgs B)
+{
+    constexpr bool SHARED = LD > 0 || NW > 0;
+    extern __shared__ uint32_t smem[];
     // lattice, tile, generation, stop; the neighbourhood to wait for: first
     // column, columns, first row, rows
     __shared__ uint32_t cmd[8];
@@ -215,43 +279,21 @@ __device__ __forceinline__ void batch_items(const BatchArgs &B, Sweep sweep)
         // the first wave took the agent-scope acquire after its waits, before
         // the barrier above (it invalidates the caches this workgroup reads
         // through, which all its waves share).
-        sweep(S, A, tile);
-        // Publish this tile's words before stamping the tile with generation
-        // g done: every lane waits until its own stores are acknowledged, the
-        // barrier orders them before thread 0, whose agent-scope release store
-        // writes them back for the other dies (once per item, not once per wave).
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (tid == 0)
-            __hip_atomic_store(&B.stamp[my_stamp], g + 1u, SHARED ? __ATOMIC_RELAXED : __ATOMIC_RELEASE,
-                               __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
-// COLS: every lattice of the launch is DB with lanes x CPT cells per domain
-// and at most 64 cells per row, so the column-mapped sweep serves them all.
-// FL > 0 (with COLS): every lattice also draws 2^FL-bit lane fields, with
-// acceptance draws iff FL = 4 and a whole number of Philox blocks of rounds,
-// so the sweep with the rounds of one block unrolled serves them all.
-//
-// LD > 0 (with COLS and FL > 0): every lattice also has square 2^LD-site
-// domains of 8 x 8-site cells, so the row-paired DB sweep serves them all.
-// LD > 0 with DTr: every lattice has square 128- or 256-site domains of
-// 8 x 8-site cells, and each item runs the row-paired DTr sweep for its
-// lattice's domain size and rates.
-//
-// DT and DTr with at most 4 cells per lane: six waves per SIMD (80 VGPRs;
-// the generic sweep spills 40 bytes to scratch for it and ran faster than
-// with the five waves its unconstrained 93 VGPRs allow; the row-paired sweep
-// fits), as do the row-paired sweeps.
-template <int SCHEME, int CPT, bool COLS, int FL, int LD>
-__global__ void __launch_bounds__(kMaxStepThreads)
-__attribute__((amdgpu_waves_per_eu((SCHEME != kDB && CPT <= 4) || LD > 0 ? 6 : 1)))
-batch_kernel(BatchArgs B)
-{
-    extern __shared__ uint32_t smem[];
-    batch_items<(LD > 0)>(B, [&](const BatchSlot &S, const StepArgs &A, uint32_t tile) {
-        if constexpr (LD > 0 && SCHEME != kDB) {
+        if constexpr (NW > 0) {
+            const bool draws = S.accept != 0u;
+            if constexpr (NW == 1) {
+                batch_dt_cells<7, NW>(A, smem, tile, draws);
+            } else if constexpr (NW == 2) {
+                if (A.Dx == 128u)
+                    batch_dt_cells<7, NW>(A, smem, tile, draws);
+                else
+                    batch_dt_cells<8, NW>(A, smem, tile, draws);
+            } else {
+                batch_dt_cells<8, NW>(A, smem, tile, draws);
+            }
+        } else if constexpr (SCHEME == kDB && LD > 0 && CPT == 1) {
+            sweep_db_cells<FL == 4, LD, true>(A, smem, tile);
+        } else if constexpr (LD > 0 && SCHEME != kDB) {
             if (A.Dx == 256u) {
                 if (S.accept)
                     sweep_dt_rows<true, CPT, 8, 3, true>(A, smem, tile);
@@ -278,47 +320,16 @@ batch_kernel(BatchArgs B)
             else
                 sweep_tile<SCHEME, false, CPT, false>(A, smem, tile);
         }
-    });
-}
-
-// DB members with one cell per lane (db_cells.hpp), square 2^LD-site domains.
-template <bool ACCEPT, int LD>
-__global__ void __launch_bounds__(CellLaneShape<LD>::NT) batch_db_cells_kernel(BatchArgs B)
-{
-    extern __shared__ uint32_t smem[];
-    batch_items<true>(B, [&](const BatchSlot &, const StepArgs &A, uint32_t tile) {
-        sweep_db_cells<ACCEPT, LD, true>(A, smem, tile);
-    });
-}
-
-// DT members that all hold their domains in registers (dt_cells.hpp), NW waves
-// per workgroup: 128-site domains for one or two, 256-site ones for two or four.
-template <int NW>
-__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 2 ? 4 : 6)))
-batch_dt_cells_kernel(BatchArgs B)
-{
-    extern __shared__ uint32_t smem[];
-    batch_items<true>(B, [&](const BatchSlot &S, const StepArgs &A, uint32_t tile) {
-        auto run = [&](auto ldc) {
-            constexpr int LD = decltype(ldc)::value;
-            if (S.accept)
-                sweep_dt_cells<kDraw, LD, NW, true>(A, smem, tile);
-            else if (A.flip_table == kFlipMin)
-                sweep_dt_cells<kDeposit, LD, NW, true>(A, smem, tile);
-            else
-                sweep_dt_cells<kSure, LD, NW, true>(A, smem, tile);
-        };
-        if constexpr (NW == 1) {
-            run(std::integral_constant<int, 7>());
-        } else if constexpr (NW == 2) {
-            if (A.Dx == 128u)
-                run(std::integral_constant<int, 7>());
-            else
-                run(std::integral_constant<int, 8>());
-        } else {
-            run(std::integral_constant<int, 8>());
-        }
-    });
+        // Publish this tile's words before stamping the tile with generation
+        // g done: every lane waits until its own stores are acknowledged, the
+        // barrier orders them before thread 0, whose agent-scope release store
+        // writes them back for the other dies (once per item, not once per wave).
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (tid == 0)
+            __hip_atomic_store(&B.stamp[my_stamp], g + 1u, SHARED ? __ATOMIC_RELAXED : __ATOMIC_RELEASE,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 __global__ void batch_reset_kernel(uint32_t *stamp, uint32_t n, unsigned long long *ticket)
@@ -534,10 +545,10 @@ int grow_tables(okpz_batch *b, size_t nslots, size_t nphases, size_t ntiles)
     return OKPZ_OK;
 }
 
-template <int SCHEME, int CPT, bool COLS, int FL = 0, int LD = 0>
+template <int SCHEME, int CPT, bool COLS, int FL = 0, int LD = 0, int NW = 0>
 const void *batch_fn()
 {
-    return reinterpret_cast<const void *>(&batch_kernel<SCHEME, CPT, COLS, FL, LD>);
+    return reinterpret_cast<const void *>(&batch_kernel<SCHEME, CPT, COLS, FL, LD, NW>);
 }
 
 const void *batch_kernel_for(int scheme, uint32_t cpt, bool cols, int fl, int ld)
@@ -878,13 +889,11 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
         if (db_cells_few(slots[0].a.Dx, b->threads, prefix[n], (uint32_t)std::max(cus, 1))) {
             const bool draws = fl == 4;
             if (ld == 8) {
-                fn = draws ? reinterpret_cast<const void *>(&batch_db_cells_kernel<true, 8>)
-                           : reinterpret_cast<const void *>(&batch_db_cells_kernel<false, 8>);
+                fn = draws ? batch_fn<kDB, 1, true, 4, 8>() : batch_fn<kDB, 1, true, 3, 8>();
                 nt = CellLaneShape<8>::NT;
                 lds = 4u * CellLaneShape<8>::LDS_WORDS;
             } else {
-                fn = draws ? reinterpret_cast<const void *>(&batch_db_cells_kernel<true, 7>)
-                           : reinterpret_cast<const void *>(&batch_db_cells_kernel<false, 7>);
+                fn = draws ? batch_fn<kDB, 1, true, 4, 7>() : batch_fn<kDB, 1, true, 3, 7>();
                 nt = CellLaneShape<7>::NT;
                 lds = 4u * CellLaneShape<7>::LDS_WORDS;
             }
@@ -909,9 +918,9 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
         ld = 8;
         lds = 4u * (any256 ? (nw == 2u ? CellShape<8, 2>::LDS_WORDS : CellShape<8, 4>::LDS_WORDS)
                            : CellShape<7, 1>::LDS_WORDS);
-        fn = nw == 1u   ? reinterpret_cast<const void *>(&batch_dt_cells_kernel<1>)
-             : nw == 2u ? reinterpret_cast<const void *>(&batch_dt_cells_kernel<2>)
-                        : reinterpret_cast<const void *>(&batch_dt_cells_kernel<4>);
+        fn = nw == 1u   ? batch_fn<kDT, 1, false, 0, 8, 1>()
+             : nw == 2u ? batch_fn<kDT, 1, false, 0, 8, 2>()
+                        : batch_fn<kDT, 1, false, 0, 8, 4>();
     }
     if (!fn) return OKPZ_EINVAL;
     if (lds > 64u * 1024u)

@@ -23,8 +23,10 @@ __device__ __forceinline__ uint32_t perm_element(uint32_t pick, uint32_t k)
 }
 
 // Tiling origin of MCS m and the word w whose third element picks the order of
-// the domain sets.
-__device__ __forceinline__ u32x4 mcs_origin(const StepArgs &A, int32_t origin_mode, uint64_t m, uint32_t &ox,
+// the domain sets.  origin_mode by reference, read where it is used: by value
+// the batch kernels held it through the draw and spilled up to seven scalar
+// registers more.
+__device__ __forceinline__ u32x4 mcs_origin(const StepArgs &A, const uint32_t &origin_mode, uint64_t m, uint32_t &ox,
                                             uint32_t &oy)
 {
     const u32x4 w = philox4x32_10(A.key0, A.key1, 0u, 0xFFFFFFFFu, 0xFFFFFFFFu, (uint32_t)(m << 2));

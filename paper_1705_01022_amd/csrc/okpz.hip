@@ -222,7 +222,7 @@ int launch_step(okpz_lattice *lat, const StepArgs &a, bool accept)
 // n MCS of a small lattice (small_lattice.hpp)
 int launch_small(okpz_lattice *lat, const StepArgs &a, bool accept, uint32_t n)
 {
-    const int om = lat->prm.origin_mode;
+    const uint32_t om = (uint32_t)lat->prm.origin_mode;
     switch (lat->prm.block_scheme * 2 + (accept ? 1 : 0)) {
     case 0: hipLaunchKernelGGL((run_small_kernel<kDT, false>), dim3(1), dim3(64), 0, lat->stream, a, lat->mcs, n, om); break;
     case 1: hipLaunchKernelGGL((run_small_kernel<kDT, true>), dim3(1), dim3(64), 0, lat->stream, a, lat->mcs, n, om); break;

@@ -20,7 +20,7 @@ constexpr uint32_t kSmallLatticeL = 128;
 constexpr uint32_t kSmallFieldPitch = 33;  // 32 words a tile; odd, so that tiles read from different banks
 
 template <int SCHEME, bool ACCEPT>
-__global__ void __launch_bounds__(64) run_small_kernel(StepArgs A, uint64_t mcs0, uint32_t n_mcs, int32_t origin_mode)
+__global__ void __launch_bounds__(64) run_small_kernel(StepArgs A, uint64_t mcs0, uint32_t n_mcs, uint32_t origin_mode)
 {
     // what the launch rule fixes, as constants
     A.log2Cx = A.log2Cy = 3u;

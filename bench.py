@@ -213,6 +213,7 @@ def batched_comparison(okpz, n_batched=200, n_plain=4, tune_mcs=10):
     el_b = time.perf_counter() - t0
     gpu_ms = b.get_timing()["ms"]
     b.timing(False)
+    shape = b.launch_shape()
     # measuring the whole ensemble: one batched pass (W^2, C_h, C_s of every
     # member in three launches) against one pass per member
     b.snapshot()
@@ -238,7 +239,9 @@ def batched_comparison(okpz, n_batched=200, n_plain=4, tune_mcs=10):
             "sites": sites, "batched_attempts_per_s": batched, "batched_mcs": n_batched,
             "batched_kernel_ms": gpu_ms, "plain_attempts_per_s": plain, "plain_mcs": n_plain,
             "batched_over_plain": batched / plain,
-            "launch_shape": {"threads": best[0], "grid_fraction": best[1], "graph": best[2]},
+            "launch_shape": {"threads": shape["threads"], "cells_per_lane": shape["cells"],
+                             "workgroups": shape["workgroups"], "configured_threads": best[0],
+                             "grid_fraction": best[1], "graph": best[2]},
             "tuner_ms": {"%d/%.2f/%s" % k: v for k, v in tuned["times_ms"].items()},
             "observe_all_ms": {"batched": 1e3 * el_ob, "per_member": 1e3 * el_ol}}
 

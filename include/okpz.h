@@ -333,6 +333,10 @@ int okpz_get_params(const okpz_lattice *lat, okpz_params *out);
 /* Wait for all queued work of the handle. */
 int okpz_sync(okpz_lattice *lat);
 
+/* Shape of the last device step launched for the lattice (0 before the first):
+ * lanes per workgroup and thread cells per lane. */
+int okpz_launch_shape(const okpz_lattice *lat, uint32_t *threads, uint32_t *cells);
+
 /*
  * Per-kernel timing with HIP events recorded on the handle's stream around
  * every launch of the device-step kernel (four per MCS, also where small
@@ -423,6 +427,12 @@ int okpz_batch_run(okpz_batch *batch, const uint64_t *n_mcs, const double *p, co
  * dependency wait (the members' lattices are then undefined and the batch
  * refuses further runs). */
 int okpz_batch_sync(okpz_batch *batch);
+
+/* Shape of the batch's last launch (0 before the first): lanes per workgroup,
+ * thread cells per lane of the largest domain, persistent workgroups, dynamic
+ * LDS of each in bytes. */
+int okpz_batch_launch_shape(const okpz_batch *batch, uint32_t *threads, uint32_t *cells, uint32_t *workgroups,
+                            uint32_t *lds_bytes);
 
 /* HIP-event timing of the batch launches (as okpz_timing); get_timing
  * returns total milliseconds, launches and update attempts since enabled. */

@@ -160,6 +160,7 @@ _SIGS = {
     "okpz_set_threads": (ctypes.c_int, [_P, ctypes.c_uint32]),
     "okpz_sync": (ctypes.c_int, [_P]),
     "okpz_timing": (ctypes.c_int, [_P, ctypes.c_int]),
+    "okpz_launch_shape": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_uint32), ctypes.POINTER(ctypes.c_uint32)]),
     "okpz_get_timing": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_double),
                                         ctypes.POINTER(ctypes.c_uint64),
                                         ctypes.POINTER(ctypes.c_double),
@@ -181,6 +182,10 @@ _SIGS = {
     "okpz_batch_series": (ctypes.c_int, [_P, _P, ctypes.c_size_t, _P, _P,
                                           ctypes.POINTER(Moments), ctypes.POINTER(Correlation)]),
     "okpz_batch_timing": (ctypes.c_int, [_P, ctypes.c_int]),
+    "okpz_batch_launch_shape": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_uint32),
+                                                ctypes.POINTER(ctypes.c_uint32),
+                                                ctypes.POINTER(ctypes.c_uint32),
+                                                ctypes.POINTER(ctypes.c_uint32)]),
     "okpz_batch_get_timing": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_double),
                                               ctypes.POINTER(ctypes.c_uint64),
                                               ctypes.POINTER(ctypes.c_uint64)]),
@@ -403,6 +408,12 @@ class Lattice:
         return {"step_ms": sm.value, "step_launches": sn.value,
                 "measure_ms": mm.value, "measure_launches": mn.value}
 
+    def launch_shape(self) -> dict:
+        """Lanes per workgroup and cells per lane of the last device step launched."""
+        t, c = ctypes.c_uint32(), ctypes.c_uint32()
+        _check(load().okpz_launch_shape(self._h, ctypes.byref(t), ctypes.byref(c)), "okpz_launch_shape")
+        return {"threads": t.value, "cells": c.value}
+
 
 def _moments_dict(m) -> dict:
     return {"mcs": m.mcs, "n_even": m.n_even, "n_odd": m.n_odd,
@@ -562,6 +573,13 @@ class Batch:
         _check(load().okpz_batch_get_timing(self._h, ctypes.byref(ms), ctypes.byref(nl), ctypes.byref(na)),
                "okpz_batch_get_timing")
         return {"ms": ms.value, "launches": nl.value, "attempts": na.value}
+
+    def launch_shape(self) -> dict:
+        """Lanes per workgroup, cells per lane (largest domain), workgroups and LDS bytes of the last launch."""
+        t, c, w, s = (ctypes.c_uint32() for _ in range(4))
+        _check(load().okpz_batch_launch_shape(self._h, ctypes.byref(t), ctypes.byref(c), ctypes.byref(w),
+                                              ctypes.byref(s)), "okpz_batch_launch_shape")
+        return {"threads": t.value, "cells": c.value, "workgroups": w.value, "lds_bytes": s.value}
 
     def tune(self, n_mcs, p, q, candidates=None) -> dict:
         """Autotune the launch shape on real work: run ``n_mcs`` (per member)

@@ -438,6 +438,7 @@ struct okpz_batch {
     uint32_t threads = 0;  // 0: 256
     uint32_t grid = 0;     // 0: as many workgroups as fit on the device at once
     bool use_graph = true;
+    uint32_t ran_threads = 0, ran_cells = 0, ran_grid = 0, ran_lds = 0;  // shape of the last launch
     // device tables
     BatchSlot *d_slots = nullptr;
     uint32_t *d_prefix = nullptr;
@@ -915,6 +916,7 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
         uint32_t nw = any256 ? dt_cells_waves(256u, b->threads, prefix[n], (uint32_t)std::max(cus, 1)) : 1u;
         if (any128 && any256) nw = 2u;
         nt = 64u * nw;
+        cpt = max_cells / nt;
         ld = 8;
         lds = 4u * (any256 ? (nw == 2u ? CellShape<8, 2>::LDS_WORDS : CellShape<8, 4>::LDS_WORDS)
                            : CellShape<7, 1>::LDS_WORDS);
@@ -1053,6 +1055,10 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
     }
     b->launches += 1;
     b->attempts += attempts;
+    b->ran_threads = nt;
+    b->ran_cells = cpt;
+    b->ran_grid = grid;
+    b->ran_lds = (uint32_t)lds;
     return OKPZ_OK;
 }
 
@@ -1113,6 +1119,17 @@ int okpz_batch_timing(okpz_batch *b, int enable)
     b->timing = enable != 0;
     b->launches = 0;
     b->attempts = 0;
+    return OKPZ_OK;
+}
+
+int okpz_batch_launch_shape(const okpz_batch *b, uint32_t *threads, uint32_t *cells, uint32_t *workgroups,
+                            uint32_t *lds_bytes)
+{
+    if (!b) return OKPZ_EINVAL;
+    if (threads) *threads = b->ran_threads;
+    if (cells) *cells = b->ran_cells;
+    if (workgroups) *workgroups = b->ran_grid;
+    if (lds_bytes) *lds_bytes = b->ran_lds;
     return OKPZ_OK;
 }
 

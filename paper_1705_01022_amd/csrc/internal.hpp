@@ -73,6 +73,7 @@ struct okpz_lattice {
     __int128 snap_s1 = 0;
     uint32_t threads = 0;  // device-step workgroup size (0: by the number of tiles per step)
     uint32_t cus = 0;      // compute units of the device
+    uint32_t ran_threads = 0, ran_cells = 0;  // shape of the last step launched: lanes, cells per lane
     // timing
     bool timing = false;
     std::vector<okpz_host::TimedPair> pairs;

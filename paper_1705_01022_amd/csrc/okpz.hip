@@ -193,12 +193,16 @@ int launch_step(okpz_lattice *lat, const StepArgs &a, bool accept)
         const int rc = launch_db_cells(ntiles, lat->stream, a, accept);
         if (rc != OKPZ_OK) return rc;
         HIP_TRY(hipGetLastError());
+        lat->ran_threads = ncell;
+        lat->ran_cells = 1;
         return OKPZ_OK;
     }
     if (dt_cells_shape(p)) {
         const int rc = launch_dt_cells(lat, ntiles, a, accept);
         if (rc != OKPZ_OK) return rc;
         HIP_TRY(hipGetLastError());
+        lat->ran_threads = 64u * dt_cells_waves(a.Dx, lat->threads, ntiles, lat->cus);
+        lat->ran_cells = ncell / lat->ran_threads;
         return OKPZ_OK;
     }
     uint32_t cpt, nt;
@@ -216,6 +220,8 @@ int launch_step(okpz_lattice *lat, const StepArgs &a, bool accept)
     }
     if (rc != OKPZ_OK) return rc;
     HIP_TRY(hipGetLastError());
+    lat->ran_threads = nt;
+    lat->ran_cells = cpt;
     return OKPZ_OK;
 }
 
@@ -232,6 +238,8 @@ int launch_small(okpz_lattice *lat, const StepArgs &a, bool accept, uint32_t n)
     default: hipLaunchKernelGGL((run_small_kernel<kDTR, true>), dim3(1), dim3(64), 0, lat->stream, a, lat->mcs, n, om); break;
     }
     HIP_TRY(hipGetLastError());
+    lat->ran_threads = 64;
+    lat->ran_cells = 1;
     return OKPZ_OK;
 }
 
@@ -944,6 +952,14 @@ int okpz_timing(okpz_lattice *lat, int enable)
     }
     lat->pairs.clear();
     lat->timing = enable != 0;
+    return OKPZ_OK;
+}
+
+int okpz_launch_shape(const okpz_lattice *lat, uint32_t *threads, uint32_t *cells)
+{
+    if (!lat) return OKPZ_EINVAL;
+    if (threads) *threads = lat->ran_threads;
+    if (cells) *cells = lat->ran_cells;
     return OKPZ_OK;
 }
 

@@ -319,7 +319,10 @@ int okpz_get_mcs(const okpz_lattice *lat, uint64_t *mcs);
  * cells (at most 16, else OKPZ_EINVAL).  Kernels made for a shape set their
  * own: DT on square 128- or 256-site domains of 8 x 8-site cells runs one
  * wave a tile (D = 128), two (D = 256, threads of 64 or 128, or 0 with many
- * tiles) or four; DB on the same domains, with 0 and few tiles (D = 128: also
+ * tiles) or four, but with acceptance draws and fewer tiles than four per
+ * compute unit what is asked for, from two cells per thread on (0: two), as
+ * it does with one cell per thread asked for (D = 128, 256 threads and more);
+ * DB on the same domains, with 0 and few tiles (D = 128: also
  * 256), one cell per thread; and with 0 lattices of L <= 128 with such cells
  * run whole MCS in one launch of one wave.  A physical mapping only: the simulated
  * lattice does not depend on it (every random draw is keyed by cell, not by

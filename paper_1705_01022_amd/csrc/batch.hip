@@ -101,8 +101,8 @@ __device__ __forceinline__ StepArgs uniform(const StepArgs &a)
 // LD > 0 (with COLS and FL > 0): every lattice also has square 2^LD-site
 // domains of 8 x 8-site cells, so the row-paired DB sweep serves them all, or,
 // with CPT = 1, the one with a cell per lane (db_cells.hpp).
-// LD > 0 with DTr: every lattice has square 128- or 256-site domains of
-// 8 x 8-site cells, and each item runs the row-paired DTr sweep for its
+// LD > 0 with DT or DTr: every lattice has square 128- or 256-site domains of
+// 8 x 8-site cells, and each item runs the row-paired DT sweep for its
 // lattice's domain size and rates.
 //
 // DT and DTr with at most 4 cells per lane: six waves per SIMD (80 VGPRs;
@@ -296,14 +296,14 @@ batch_kernel(BatchArgs B)
         } else if constexpr (LD > 0 && SCHEME != kDB) {
             if (A.Dx == 256u) {
                 if (S.accept)
-                    sweep_dt_rows<true, CPT, 8, 3, true>(A, smem, tile);
+                    sweep_dt_rows<SCHEME, true, CPT, 8, 3, true>(A, smem, tile);
                 else
-                    sweep_dt_rows<false, CPT, 8, 3, true>(A, smem, tile);
+                    sweep_dt_rows<SCHEME, false, CPT, 8, 3, true>(A, smem, tile);
             } else {
                 if (S.accept)
-                    sweep_dt_rows<true, CPT, 7, 3, true>(A, smem, tile);
+                    sweep_dt_rows<SCHEME, true, CPT, 7, 3, true>(A, smem, tile);
                 else
-                    sweep_dt_rows<false, CPT, 7, 3, true>(A, smem, tile);
+                    sweep_dt_rows<SCHEME, false, CPT, 7, 3, true>(A, smem, tile);
             }
         } else if constexpr (LD > 0) {
             sweep_db_rows<FL == 4, CPT, LD, 3, true>(A, smem, tile);
@@ -554,7 +554,8 @@ const void *batch_fn()
 
 const void *batch_kernel_for(int scheme, uint32_t cpt, bool cols, int fl, int ld)
 {
-    if (scheme != kDB && ld) {
+    if (scheme == kDT && ld) return cpt == 1 ? batch_fn<kDT, 1, false, 0, 8>() : batch_fn<kDT, 2, false, 0, 8>();
+    if (scheme == kDTR && ld) {
         switch (cpt) {
         case 1: return batch_fn<kDTR, 1, false, 0, 8>();
         case 2: return batch_fn<kDTR, 2, false, 0, 8>();
@@ -866,15 +867,30 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
         if (ld == 8) lds = 4u * rowpair_lds_words<8, 3>(nt);
         if (ld == 7) lds = 4u * rowpair_lds_words<7, 3>(nt);
     }
-    // DTr with square 128- or 256-site domains of 8 x 8-site cells throughout,
-    // at most four cells per lane: the row-paired sweep (the window alone in LDS)
-    if (b->scheme == kDTR && cpt <= 4) {
-        bool rows = true, any256 = false;
+    // DT members that all can hold their domains in registers, and whether they
+    // take the row-paired sweep all the same (their larger domains decide)
+    bool regs = b->scheme == kDT, draws = false, any128 = false, any256 = false;
+    for (uint32_t i = 0; i < n; ++i) {
+        const okpz_params &prm = b->slots[order[i]]->prm;
+        regs = regs && dt_cells_shape(prm);
+        draws = draws || slots[i].accept != 0u;
+        any128 = any128 || prm.dom_x == 128u;
+        any256 = any256 || prm.dom_x == 256u;
+    }
+    int dev = 0, cus = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    cus = std::max(cus, 1);
+    const bool dt_rows =
+        regs && cpt <= 2 && dt_rows_few(any256 ? 256u : 128u, b->threads, draws, prefix[n], (uint32_t)cus);
+    // DTr (and DT by that rule) with square 128- or 256-site domains of 8 x 8-site cells
+    // throughout, at most four cells per lane: the row-paired sweep (the window alone in LDS)
+    if (dt_rows || (b->scheme == kDTR && cpt <= 4)) {
+        bool rows = true;
         for (uint32_t i = 0; i < n && rows; ++i) {
             const StepArgs &a = slots[i].a;
             rows = a.Dx == a.Dy && (a.Dx == 256u || a.Dx == 128u) && a.log2Cx == 3u && a.log2Cy == 3u &&
                    a.s_bits == 4u && !a.shared_edges && a.F_log2 == (slots[i].accept ? 4u : 2u);
-            any256 = any256 || a.Dx == 256u;
         }
         if (rows) {
             ld = 8;
@@ -884,11 +900,7 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
     const void *fn = batch_kernel_for(b->scheme, cpt, cols, fl, ld);
     // few tiles of DB members that the row-paired sweep would serve: one cell per lane
     if (ld && b->scheme == kDB) {
-        int dev = 0, cus = 0;
-        HIP_TRY(hipGetDevice(&dev));
-        HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        if (db_cells_few(slots[0].a.Dx, b->threads, prefix[n], (uint32_t)std::max(cus, 1))) {
-            const bool draws = fl == 4;
+        if (db_cells_few(slots[0].a.Dx, b->threads, prefix[n], (uint32_t)cus)) {
             if (ld == 8) {
                 fn = draws ? batch_fn<kDB, 1, true, 4, 8>() : batch_fn<kDB, 1, true, 3, 8>();
                 nt = CellLaneShape<8>::NT;
@@ -902,18 +914,8 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
         }
     }
     // DT members that all hold their domains in registers
-    bool regs = true, any128 = false, any256 = false;
-    for (int32_t s : order) {
-        const okpz_params &prm = b->slots[s]->prm;
-        regs = regs && dt_cells_shape(prm);
-        any128 = any128 || prm.dom_x == 128u;
-        any256 = any256 || prm.dom_x == 256u;
-    }
-    if (regs) {
-        int dev = 0, cus = 0;
-        HIP_TRY(hipGetDevice(&dev));
-        HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        uint32_t nw = any256 ? dt_cells_waves(256u, b->threads, prefix[n], (uint32_t)std::max(cus, 1)) : 1u;
+    if (regs && !dt_rows) {
+        uint32_t nw = any256 ? dt_cells_waves(256u, b->threads, prefix[n], (uint32_t)cus) : 1u;
         if (any128 && any256) nw = 2u;
         nt = 64u * nw;
         cpt = max_cells / nt;
@@ -929,10 +931,8 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
         HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kMaxLds - kStaticLds)));
     uint32_t grid = b->grid;
     if (grid == 0) {
-        int per_cu = 0, dev = 0, cus = 0;
+        int per_cu = 0;
         HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, (int)nt, lds));
-        HIP_TRY(hipGetDevice(&dev));
-        HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
         grid = (uint32_t)std::max(1, per_cu * cus);
         // no more workgroups than tiles in one step of all members: a workgroup
         // beyond them would only wait for the next step's dependencies while

@@ -35,7 +35,7 @@ namespace okpz {
 
 // Compile-time geometry of a square D x D domain (LD = log2 D >= 5) with
 // C x C-site cells (LC = log2 C): the same window as window_shape() on the
-// host (NWX blocks, NB bands).  WIDE: the DTr step's row pitch (below).
+// host (NWX blocks, NB bands).  WIDE: the DT / DTr step's row pitch (below).
 template <int LD, int LC, bool WIDE = false>
 struct RowPairShape {
     static constexpr uint32_t D = 1u << LD;
@@ -50,7 +50,7 @@ struct RowPairShape {
     static constexpr uint32_t NR = 4 * NB;
     // words per window row (sx words, sy words, padding), chosen against LDS
     // bank conflicts (32 banks; the 32 lanes of a half-wave hold one cell
-    // row): 2P + 1 below D = 256.  At D = 256, DTr (WIDE): 24 words,
+    // row): 2P + 1 below D = 256.  At D = 256, DT / DTr (WIDE): 24 words,
     // which puts the four rows of a quadrant on the bank offsets 0, 24, 16
     // and 8, so that the eight words a cell row's attempts reach in each of
     // them fall on distinct banks (the window then leaves room for six

@@ -1,21 +1,22 @@
-// DTr device step on the row-paired LDS window of the DB kernel (square
-// domains of 128 or 256 sites, 8 x 8-site cells).  Same attempts and random
-// draws as sweep_tile's DTr path (Sec. 3 DTr at block level, Sec. 3.1 single
-// hit): in round rho every cell attempts one site of the quadrant its block
-// draw names, of its cell in the shifted cell grid, so the attempts of one
-// round touch pairwise disjoint slopes and need no ordering among themselves;
-// a barrier separates the rounds.  What changes is how an attempt is found and
-// tested -- one LDS address for its four slope words, linear site indices,
-// acceptance after the slope pattern (attempt_rows) -- with every domain-sized
-// quantity compile-time.  (DT, whose cell grid stands still, holds its domain
-// in registers: dt_cells.hpp.)
+// DT and DTr device steps on the row-paired LDS window of the DB kernel
+// (square domains of 128 or 256 sites, 8 x 8-site cells).  Same attempts and
+// random draws as sweep_tile's DT / DTr path (Sec. 3 DT and DTr at block
+// level, Sec. 3.1 single hit): in round rho every cell attempts one site of
+// the quadrant its block draw names (DTr: of its cell in the shifted cell
+// grid), so the attempts of one round touch pairwise disjoint slopes and
+// need no ordering among themselves; a barrier separates the rounds.  What
+// changes is how an attempt is found and tested -- one LDS address for its
+// four slope words, linear site indices, acceptance after the slope pattern
+// (attempt_rows) -- with every domain-sized quantity compile-time.  DT, whose
+// cell grid stands still, mostly holds its domain in registers instead
+// (dt_cells.hpp); it comes here where dt_rows_few() says so, with few tiles.
 #pragma once
 
 #include "db_rows.hpp"
 
 namespace okpz {
 
-// LDS words of the row-paired DTr step: the window alone (wide rows).
+// LDS words of the row-paired DT / DTr step: the window alone (wide rows).
 template <int LD, int LC>
 __host__ __device__ constexpr uint32_t rowpair_dt_lds_words()
 {
@@ -26,7 +27,7 @@ __host__ __device__ constexpr uint32_t rowpair_dt_lds_words()
 // stacked vertically, so the lanes of one instruction sit side by side in
 // one or two cell rows.  Lane-draw fields are 2^FL bits (16 with acceptance
 // prefixes, 4 without), the rounds of one Philox block unrolled.
-template <bool ACCEPT, int CPT, int LD, int LC, bool SHARED>
+template <int SCHEME, bool ACCEPT, int CPT, int LD, int LC, bool SHARED>
 __device__ __forceinline__ void sweep_dt_rows(const StepArgs &A, uint32_t *smem, uint32_t tile)
 {
     using S = RowPairShape<LD, LC, true>;
@@ -80,17 +81,23 @@ __device__ __forceinline__ void sweep_dt_rows(const StepArgs &A, uint32_t *smem,
         for (int k = 0; k < RPB; ++k) {
             const uint32_t rho = blk * RPB + k;
             const uint32_t f16 = next_block_field(draws, bd, rho);
-            // the round's quadrant and the shift of the cell grid
-            const uint32_t cu = base_u + ((f16 & 1u) << QL) + ((f16 >> 2) & (S::C - 1u));
-            const uint32_t cv = base_v0 + (((f16 >> 1) & 1u) << QL) + ((f16 >> 8) & (S::C - 1u));
+            // the round's quadrant (and, DTr, the shift of the cell grid)
+            uint32_t cu = base_u + ((f16 & 1u) << QL), cv = base_v0 + (((f16 >> 1) & 1u) << QL);
+            if (SCHEME == kDTR) {
+                cu += (f16 >> 2) & (S::C - 1u);
+                cv += (f16 >> 8) & (S::C - 1u);
+            }
 #pragma unroll
             for (int j = CPT - 1; j >= 0; --j) {
                 const uint32_t f = field_of(w[j], k);
-                // the shifted grid wraps around the domain; only a lane's
-                // bottom cell can be in the last cell row
-                const uint32_t u = (cu + (f & QM)) & (S::D - 1u);
+                uint32_t u = cu + (f & QM);
                 uint32_t v = cv + (j << LC) + ((f >> QL) & QM);
-                if (j == CPT - 1) v &= S::D - 1u;
+                if (SCHEME == kDTR) {
+                    // the shifted grid wraps around the domain; only a lane's
+                    // bottom cell can be in the last cell row
+                    u &= S::D - 1u;
+                    if (j == CPT - 1) v &= S::D - 1u;
+                }
                 const uint32_t s = __umul24(v, S::ROW) + u + origin;
                 attempt_rows<ACCEPT, P, S::PITCH>(A, s, f >> SBITS, act, rho, cell0 + j * S::NCX, tile);
             }
@@ -100,13 +107,13 @@ __device__ __forceinline__ void sweep_dt_rows(const StepArgs &A, uint32_t *smem,
     store_window_rows<S, NTC, SHARED>(A, lds, X0 >> 5, Y0 >> 2);
 }
 
-// The DTr device-step kernel on the row-paired window.
-template <bool ACCEPT, int CPT, int LD, int LC>
+// The DT / DTr device-step kernel on the row-paired window.
+template <int SCHEME, bool ACCEPT, int CPT, int LD, int LC>
 __global__ void __launch_bounds__(kMaxStepThreads) __attribute__((amdgpu_waves_per_eu(7)))
 step_dt_rows_kernel(StepArgs A)
 {
     extern __shared__ uint32_t smem[];
-    sweep_dt_rows<ACCEPT, CPT, LD, LC, false>(A, smem, blockIdx.x);
+    sweep_dt_rows<SCHEME, ACCEPT, CPT, LD, LC, false>(A, smem, blockIdx.x);
 }
 
 }  // namespace okpz

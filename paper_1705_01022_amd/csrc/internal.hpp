@@ -285,7 +285,25 @@ inline bool db_cells_few(uint32_t dom, uint32_t threads, uint64_t ntiles, uint32
     return ntiles <= (dom == 128u ? 4ull : 1ull) * cus;
 }
 
-// Waves per tile of that step: one for 128-site domains (two leave a lane one
+// Whether the DT step takes the row-paired kernel of the DTr step instead (which
+// has more lanes a tile; dt_rows.hpp): with few tiles and acceptance draws, where a
+// round waits for the draws of a lane's many cells, unless a workgroup of fewer
+// lanes than two cells each is asked for, and 128-site domains with a lane per
+// cell asked for.  us an MCS, p = 0.7, registers against rows: D = 256, one tile
+// 154 and 118, 64 tiles 165 and 125, 256 171 and 131, 1024 279 and 271, 4096 788
+// and 912; batches of 32 tiles 175 and 132, 400 196 and 153, 1000 267 and 254, 1600
+// 356 and 390; D = 128 (128 lanes), one tile 115 and 96, 1024 137 and 120, 4096 250
+// and 276; with 256 lanes, p = 1, one tile 72 and 54, 64 75 and 57, 1024 90 and 97
+// (in a batch 100 and 86).  With p = 1 otherwise D = 256 88 and 97, D = 128 72 and 75.
+inline bool dt_rows_few(uint32_t dom, uint32_t threads, bool draws, uint64_t ntiles, uint32_t cus)
+{
+    if (ntiles >= 4ull * cus) return false;
+    const uint32_t ncell = dom * dom / 64u;
+    if (threads && threads < ncell / 2u) return false;
+    return draws || threads >= ncell;
+}
+
+// Waves per tile of the DT step in registers: one for 128-site domains (two leave a lane one
 // pair of cells: L = 2^16 at p = 1 0.79 ms a launch against 0.47); for 256-site
 // domains two, or four when a step has fewer tiles than four per compute unit
 // (p = 1, two against four: 1024 tiles 48 against 51 us, 256 tiles 34 against

@@ -79,24 +79,28 @@ bool launch_db_rows(uint32_t nt, uint32_t ntiles, hipStream_t st, const StepArgs
     return false;
 }
 
-// The row-paired DTr kernel for square 128- or 256-site domains of 8 x 8-site
-// cells (4 site bits per lane draw, in 16-bit fields with acceptance
-// prefixes, 4-bit fields without), one to four cells per lane.
-template <bool ACCEPT, int CPT>
-bool launch_dtr_rows(uint32_t nt, uint32_t ntiles, hipStream_t st, const StepArgs &a, int &rc)
+// The row-paired DT / DTr kernel for square 128- or 256-site domains of
+// 8 x 8-site cells (4 site bits per lane draw, in 16-bit fields with acceptance
+// prefixes, 4-bit fields without), one to four cells per lane.  DT comes here
+// in the shapes that dt_rows_few() picks only.
+template <int SCHEME, bool ACCEPT, int CPT>
+bool launch_dt_rows(uint32_t nt, uint32_t ntiles, hipStream_t st, const StepArgs &a, int &rc)
 {
-    if constexpr (CPT == 1 || CPT == 2 || CPT == 4) {
+    constexpr bool D256 = SCHEME == kDTR || (ACCEPT && CPT == 2), D128 = SCHEME == kDTR || CPT == 1 || D256;
+    if constexpr ((CPT == 1 || CPT == 2 || CPT == 4) && D128) {
         constexpr uint32_t FL = ACCEPT ? 4u : 2u;
         if (a.Dx != a.Dy || a.log2Cx != 3u || a.log2Cy != 3u || a.s_bits != 4u || a.F_log2 != FL ||
             a.shared_edges)
             return false;
-        if (a.Dx == 256u) {
-            rc = launch_instance(&step_dt_rows_kernel<ACCEPT, CPT, 8, 3>, nt, ntiles,
-                                 4u * rowpair_dt_lds_words<8, 3>(), st, a);
-            return true;
+        if constexpr (D256) {
+            if (a.Dx == 256u) {
+                rc = launch_instance(&step_dt_rows_kernel<SCHEME, ACCEPT, CPT, 8, 3>, nt, ntiles,
+                                     4u * rowpair_dt_lds_words<8, 3>(), st, a);
+                return true;
+            }
         }
         if (a.Dx == 128u) {
-            rc = launch_instance(&step_dt_rows_kernel<ACCEPT, CPT, 7, 3>, nt, ntiles,
+            rc = launch_instance(&step_dt_rows_kernel<SCHEME, ACCEPT, CPT, 7, 3>, nt, ntiles,
                                  4u * rowpair_dt_lds_words<7, 3>(), st, a);
             return true;
         }
@@ -147,9 +151,9 @@ int launch_step_inst(uint32_t nt, uint32_t ntiles, size_t lds, hipStream_t st, c
     // the dead-border control runs the generic kernel (the only one that
     // masks the tiles' rims and XORs back the words they share)
     if (a.dev_db) return launch_instance(&step_kernel<SCHEME, ACCEPT, CPT>, nt, ntiles, lds, st, a);
-    if constexpr (SCHEME == kDTR) {
+    if constexpr (SCHEME != kDB) {
         int rc = OKPZ_OK;
-        if (launch_dtr_rows<ACCEPT, CPT>(nt, ntiles, st, a, rc)) return rc;
+        if (launch_dt_rows<SCHEME, ACCEPT, CPT>(nt, ntiles, st, a, rc)) return rc;
     }
     if constexpr (SCHEME == kDB && CPT >= 2) {
         int rc = OKPZ_OK;
@@ -197,7 +201,7 @@ int launch_step(okpz_lattice *lat, const StepArgs &a, bool accept)
         lat->ran_cells = 1;
         return OKPZ_OK;
     }
-    if (dt_cells_shape(p)) {
+    if (dt_cells_shape(p) && !dt_rows_few(p.dom_x, lat->threads, accept, ntiles, lat->cus)) {
         const int rc = launch_dt_cells(lat, ntiles, a, accept);
         if (rc != OKPZ_OK) return rc;
         HIP_TRY(hipGetLastError());

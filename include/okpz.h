@@ -408,7 +408,9 @@ int okpz_batch_size(const okpz_batch *batch, uint32_t *nslots);
  * largest domain's cells, at most 256, or 512 when the launch has fewer
  * tiles per step than four per compute unit, and at most half the cells of
  * a domain of 256 cells or more; the kernels made for a shape set their own
- * as for okpz_set_threads), persistent workgroups
+ * as for okpz_set_threads; DB on their domains takes two cells per thread in
+ * place of four with fewer tiles than four per compute unit, and always at
+ * D = 128), persistent workgroups
  * (0 = as many as fit on the device at once, but no more than the members'
  * tiles in one step), use_graph (capture and replay the launch).  Chosen by
  * the autotuner of the Python layer.

@@ -765,6 +765,11 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t c) { return n_mcs[a] > n_mcs[c]; });
     const uint32_t n = (uint32_t)order.size();
 
+    int dev = 0, cus = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    cus = std::max(cus, 1);
+
     // launch shape: lanes per workgroup (default: enough for the largest
     // domain's cells, 64 .. 256, at most half of them from 256 cells on),
     // cells per lane
@@ -774,14 +779,11 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
     if (nt == 0) {
         uint64_t tiles = 0;
         for (int32_t s : order) tiles += tiles_of(b->slots[s]->prm);
-        int dev = 0, cus = 0;
-        HIP_TRY(hipGetDevice(&dev));
-        HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
         // the batch's DB step keeps the larger workgroup up to eight tiles per
         // compute unit (1024 tiles of 1024 cells: 3.89 ms against 4.02 with
         // 256 lanes; 4096 tiles: 256 lanes 11.1 ms against 14.4)
         const uint64_t few = b->scheme == kDB ? (tiles + 1u) / 2u : tiles;
-        const uint32_t cap = default_threads(few, (uint32_t)std::max(cus, 1), max_cells);
+        const uint32_t cap = default_threads(few, (uint32_t)cus, max_cells);
         nt = 64;
         while (nt < cap && nt < max_cells) nt *= 2;
     }
@@ -864,6 +866,15 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
             const StepArgs &a = slots[i].a;
             if (a.Dx != d0 || a.Dy != d0 || a.log2Cx != 3u || a.log2Cy != 3u || a.s_bits != 6u) ld = 0;
         }
+        // two cells per lane, and twice the lanes, in place of four: with few tiles
+        // (D = 256, p = 0.7, us an MCS with 256 lanes and with 512: 32 tiles 366 and 256,
+        // 400 380 and 285, 800 430 and 382, 1000 461 and 437, 1200 518 and 521; 1600, p = 1
+        // 559 and 634) and always at D = 128 (64 lanes and 128, p = 1: 416 tiles 234 and
+        // 171, 4016 425 and 360)
+        if (ld && cpt == 4 && (ld == 7 || prefix[n] < 4u * (uint32_t)cus)) {
+            nt *= 2;
+            cpt = 2;
+        }
         if (ld == 8) lds = 4u * rowpair_lds_words<8, 3>(nt);
         if (ld == 7) lds = 4u * rowpair_lds_words<7, 3>(nt);
     }
@@ -877,10 +888,6 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
         any128 = any128 || prm.dom_x == 128u;
         any256 = any256 || prm.dom_x == 256u;
     }
-    int dev = 0, cus = 0;
-    HIP_TRY(hipGetDevice(&dev));
-    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    cus = std::max(cus, 1);
     const bool dt_rows =
         regs && cpt <= 2 && dt_rows_few(any256 ? 256u : 128u, b->threads, draws, prefix[n], (uint32_t)cus);
     // DTr (and DT by that rule) with square 128- or 256-site domains of 8 x 8-site cells
@@ -1002,8 +1009,7 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
     lp.args.ticket = b->d_ticket;
     lp.args.error = b->d_error;
     {
-        int dev = 0, khz = 0;
-        HIP_TRY(hipGetDevice(&dev));
+        int khz = 0;
         HIP_TRY(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
         lp.args.wait_ticks = (uint64_t)std::max(khz, 1) * 1000ull * kWaitSeconds;
     }

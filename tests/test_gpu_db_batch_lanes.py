@@ -1,0 +1,39 @@
+"""DB batches on the domains the kernels are made for keep two cells a lane, or
+one, with few tiles, whatever workgroup was asked for: the shape that ran and
+parity with the oracle's DTr emulation."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def run(okpz, orc, n, L, D, threads, p, q, check):
+    print("db batch: %d x L=%d D=%d threads=%d p=%r" % (n, L, D, threads, p), flush=True)
+    b = okpz.Batch()
+    lats = [b.lattice(L, D, D, 8, 8, okpz.BLOCK_DB, seed=8, stream=i) for i in range(n)]
+    b.config(threads, 0, True)
+    b.run([4] * n, [p] * n, [q] * n)
+    b.sync()
+    shape = b.launch_shape()
+    for i in check:
+        e = orc.Emu(L=L, Dx=D, Dy=D, Cx=8, Cy=8, scheme=orc.DB, p=p, q=q, seed=8, stream=i)
+        ref = orc.init_flat(L)
+        for m in range(4):
+            e.mcs(ref, m)
+        assert np.array_equal(lats[i].sites(), ref)
+    b.close()
+    return shape["threads"], shape["cells"]
+
+
+@pytest.mark.parametrize("p,q", [(1.0, 0.0), (0.7, 0.3)])
+def test_two_cells_with_few_tiles(okpz, orc, p, q):
+    assert run(okpz, orc, 3, 512, 256, 256, p, q, range(3)) == (512, 2)
+    assert run(okpz, orc, 3, 256, 128, 64, p, q, range(3)) == (128, 2)
+
+
+@pytest.mark.parametrize("p,q", [(1.0, 0.0), (0.7, 0.3)])
+def test_four_cells_with_many_tiles(okpz, orc, p, q):
+    cus = __import__("torch").cuda.get_device_properties(0).multi_processor_count
+    n = 4 * cus // 16 + 1  # L = 2048, D = 256: 16 tiles a step each
+    assert run(okpz, orc, n, 2048, 256, 256, p, q, (0, n - 1)) == (256, 4)
+    assert run(okpz, orc, n // 4 + 1, 2048, 128, 64, p, q, (0,)) == (128, 2)

@@ -905,20 +905,25 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
         }
     }
     const void *fn = batch_kernel_for(b->scheme, cpt, cols, fl, ld);
-    // few tiles of DB members that the row-paired sweep would serve: one cell per lane
-    if (ld && b->scheme == kDB) {
-        if (db_cells_few(slots[0].a.Dx, b->threads, prefix[n], (uint32_t)cus)) {
-            if (ld == 8) {
-                fn = draws ? batch_fn<kDB, 1, true, 4, 8>() : batch_fn<kDB, 1, true, 3, 8>();
-                nt = CellLaneShape<8>::NT;
-                lds = 4u * CellLaneShape<8>::LDS_WORDS;
-            } else {
-                fn = draws ? batch_fn<kDB, 1, true, 4, 7>() : batch_fn<kDB, 1, true, 3, 7>();
-                nt = CellLaneShape<7>::NT;
-                lds = 4u * CellLaneShape<7>::LDS_WORDS;
-            }
-            cpt = 1;
+    // DB members of one such domain and one way of deciding, with few tiles (or, D = 128,
+    // with a lane per cell asked for): one cell per lane
+    bool db_cells = b->scheme == kDB;
+    for (uint32_t i = 0; i < n && db_cells; ++i)
+        db_cells = db_cells_shape(b->slots[order[i]]->prm) && slots[i].a.Dx == slots[0].a.Dx &&
+                   slots[i].accept == slots[0].accept;
+    if (db_cells && db_cells_few(slots[0].a.Dx, b->threads, prefix[n], (uint32_t)cus)) {
+        if (any256) {
+            fn = draws ? batch_fn<kDB, 1, true, 4, 8>() : batch_fn<kDB, 1, true, 3, 8>();
+            nt = CellLaneShape<8>::NT;
+            lds = 4u * CellLaneShape<8>::LDS_WORDS;
+            ld = 8;
+        } else {
+            fn = draws ? batch_fn<kDB, 1, true, 4, 7>() : batch_fn<kDB, 1, true, 3, 7>();
+            nt = CellLaneShape<7>::NT;
+            lds = 4u * CellLaneShape<7>::LDS_WORDS;
+            ld = 7;
         }
+        cpt = 1;
     }
     // DT members that all hold their domains in registers
     if (regs && !dt_rows) {

@@ -37,3 +37,25 @@ def test_four_cells_with_many_tiles(okpz, orc, p, q):
     n = 4 * cus // 16 + 1  # L = 2048, D = 256: 16 tiles a step each
     assert run(okpz, orc, n, 2048, 256, 256, p, q, (0, n - 1)) == (256, 4)
     assert run(okpz, orc, n // 4 + 1, 2048, 128, 64, p, q, (0,)) == (128, 2)
+
+
+@pytest.mark.parametrize("p,q", [(1.0, 0.0), (0.7, 0.3)])
+def test_one_cell_per_lane(okpz, orc, p, q):
+    assert run(okpz, orc, 3, 512, 256, 0, p, q, range(3)) == (1024, 1)
+    assert run(okpz, orc, 3, 512, 128, 0, p, q, range(3)) == (256, 1)
+    # a lane per cell asked for: the same kernel, not the generic sweep of that shape
+    kernel = lambda threads: batch_shape(okpz, 3, 512, 128, threads, p, q)
+    assert kernel(256) == kernel(0)
+    assert run(okpz, orc, 3, 512, 128, 256, p, q, range(3)) == (256, 1)
+
+
+def batch_shape(okpz, n, L, D, threads, p, q):
+    b = okpz.Batch()
+    for i in range(n):
+        b.lattice(L, D, D, 8, 8, okpz.BLOCK_DB, seed=8, stream=i)
+    b.config(threads, 0, True)
+    b.run([1] * n, [p] * n, [q] * n)
+    b.sync()
+    shape = b.launch_shape()
+    b.close()
+    return shape

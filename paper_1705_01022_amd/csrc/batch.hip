@@ -779,10 +779,18 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
     if (nt == 0) {
         uint64_t tiles = 0;
         for (int32_t s : order) tiles += tiles_of(b->slots[s]->prm);
-        // the batch's DB step keeps the larger workgroup up to eight tiles per
-        // compute unit (1024 tiles of 1024 cells: 3.89 ms against 4.02 with
-        // 256 lanes; 4096 tiles: 256 lanes 11.1 ms against 14.4)
-        const uint64_t few = b->scheme == kDB ? (tiles + 1u) / 2u : tiles;
+        // the DB step keeps the larger workgroup up to eight tiles per compute unit where
+        // the domain is large, so that few workgroups share a unit's LDS (512 x 256 sites
+        // and up: 1200 tiles 1559 us an MCS with 512 lanes, 2337 with 256; 512 x 512 with
+        // 8 x 8 cells 5020 and 5540, with 16 x 16 3703 and 4820), or 256 lanes would hold
+        // eight cells each (256 x 128 sites, 4 x 4 cells: 593 and 895); not elsewhere
+        // (512 x 128, 8 x 8 cells, 1600 tiles 884 and 736; 128 x 128, 4 x 4 cells 362 and 301;
+        // 256 x 256, 4 x 4 cells 1605 and 1467, 8 x 8 cells 1440 tiles 623 and 573)
+        uint64_t sites = 0;
+        for (int32_t s : order)
+            sites = std::max(sites, (uint64_t)b->slots[s]->prm.dom_x * b->slots[s]->prm.dom_y);
+        const bool wide = b->scheme == kDB && (sites >= (1u << 17) || max_cells == 2048u);
+        const uint64_t few = wide ? (tiles + 1u) / 2u : tiles;
         const uint32_t cap = default_threads(few, (uint32_t)cus, max_cells);
         nt = 64;
         while (nt < cap && nt < max_cells) nt *= 2;

@@ -59,3 +59,26 @@ def batch_shape(okpz, n, L, D, threads, p, q):
     shape = b.launch_shape()
     b.close()
     return shape
+
+
+def default_shape(okpz, n, L, Dx, Dy, C):
+    b = okpz.Batch()
+    for i in range(n):
+        b.lattice(L, Dx, Dy, C, C, okpz.BLOCK_DB, seed=8, stream=i)
+    print("db batch: %d x L=%d %dx%d cells of %d" % (n, L, Dx, Dy, C), flush=True)
+    b.run([1] * n, [0.7] * n, [0.3] * n)
+    b.sync()
+    shape = b.launch_shape()
+    b.close()
+    return shape["threads"], shape["cells"]
+
+
+def test_default_lanes_with_many_tiles(okpz):
+    cus = __import__("torch").cuda.get_device_properties(0).multi_processor_count
+    tiles = lambda per: 4 * cus // per + 1  # lattices for a few more than four tiles per compute unit
+    assert default_shape(okpz, tiles(16), 2048, 256, 256, 8) == (256, 4)
+    assert default_shape(okpz, tiles(16), 2048, 512, 128, 8) == (256, 4)
+    assert default_shape(okpz, tiles(64), 2048, 128, 128, 4) == (256, 4)
+    # large domains and eight cells a lane: the larger workgroup
+    assert default_shape(okpz, tiles(8), 2048, 512, 256, 8) == (512, 4)
+    assert default_shape(okpz, tiles(32), 2048, 256, 128, 4) == (512, 4)

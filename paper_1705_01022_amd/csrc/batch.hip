@@ -251,8 +251,9 @@ batch_kernel(BatchArgs B)
                     }
                 }
                 const uint64_t any_bad = __ballot(bad);  // every lane of the wave takes part
-                // the earlier steps' words, written by other workgroups, become visible
-                // (the cache invalidation covers the whole workgroup's caches)
+                // generic sweeps read through the caches: the earlier steps' words, written by
+                // other workgroups, become visible (the invalidation covers the whole
+                // workgroup's caches)
                 if (!SHARED) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 if (tid == 0 && any_bad) cmd[3] = 1u;
             }
@@ -275,10 +276,15 @@ batch_kernel(BatchArgs B)
         A.set_a = set & 1u;
         A.set_b = set >> 1;
         A.c3 = (uint32_t)(m << 2) | k;
-        // Visibility of the earlier steps' words, written by other workgroups:
-        // the first wave took the agent-scope acquire after its waits, before
-        // the barrier above (it invalidates the caches this workgroup reads
-        // through, which all its waves share).
+        // Visibility of the earlier steps' words, written by other workgroups.
+        // Generic sweeps: the first wave took the agent-scope acquire after its
+        // waits, before the barrier above (it invalidates the caches this
+        // workgroup reads through, which all its waves share).  SHARED sweeps:
+        // no acquire; every load and store of lattice words in them is an
+        // agent-scope atomic (load_word, load_words, store_words), which goes to
+        // where all dies see it, and is issued after the barrier, so after the
+        // stamps were seen.  A plain access to lattice words in a SHARED sweep
+        // would break this.
         if constexpr (NW > 0) {
             const bool draws = S.accept != 0u;
             if constexpr (NW == 1) {
@@ -320,10 +326,15 @@ batch_kernel(BatchArgs B)
             else
                 sweep_tile<SCHEME, false, CPT, false>(A, smem, tile);
         }
-        // Publish this tile's words before stamping the tile with generation
-        // g done: every lane waits until its own stores are acknowledged, the
-        // barrier orders them before thread 0, whose agent-scope release store
-        // writes them back for the other dies (once per item, not once per wave).
+        // Publish this tile's words before stamping the tile with generation g
+        // done: every lane waits until its own stores are acknowledged and the
+        // barrier orders them before thread 0's stamp.  Generic sweeps: the stamp
+        // is an agent-scope release store, which writes the words back for the
+        // other dies (once per item, not once per wave).  SHARED sweeps: the
+        // acknowledged stores are there already and the stamp is relaxed; the
+        // fence of one thread, no instruction, keeps the compiler from moving
+        // them past the wait.
+        if (SHARED) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "singlethread");
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         if (tid == 0)

@@ -587,9 +587,10 @@ class Batch:
         fastest.  Every candidate's MCS really advance the members (results do
         not depend on the shape).  Returns {candidate: ms} and the choice."""
         if candidates is None:
-            # 0, the automatic size, first: some kernels are reached by it alone
-            candidates = [(0, 1.0, True), (256, 1.0, True), (128, 1.0, True), (512, 1.0, True), (256, 0.5, True),
-                          (256, 1.0, False)]
+            # 0, the automatic size: some kernels are reached by it alone; last, since
+            # the first candidate is timed before the clocks have settled
+            candidates = [(256, 1.0, True), (128, 1.0, True), (512, 1.0, True), (256, 0.5, True),
+                          (256, 1.0, False), (0, 1.0, True)]
         full = self._full_grid()
         times = {}
         for threads, frac, graph in candidates:

@@ -182,7 +182,10 @@ int okpz_create(const okpz_params *params, void *hip_stream, okpz_lattice **out)
  * As okpz_create, but the packed lattice lives in caller-owned device memory
  * `dev_words` of `nbytes` >= L*L/4 bytes (e.g. a torch tensor), 256-byte
  * aligned.  The caller keeps it alive until okpz_destroy.  The contents are
- * overwritten with the flat state.
+ * overwritten with the flat state.  A caller that writes the words itself
+ * writes a periodic surface (as okpz_init_from_host demands of its sites): a
+ * step may work out slopes from their neighbours and writes all of a
+ * domain's, so of words that are no surface nothing is kept.
  */
 int okpz_create_external(const okpz_params *params, void *hip_stream, void *dev_words,
                          size_t nbytes, okpz_lattice **out);

@@ -947,6 +947,9 @@ int batch_run_once(okpz_batch *b, const uint64_t *n_mcs, const double *p, const 
     // DT members that all hold their domains in registers
     if (regs && !dt_rows) {
         uint32_t nw = any256 ? dt_cells_waves(256u, b->threads, prefix[n], (uint32_t)cus) : 1u;
+        // both sizes: two waves, which 128-site members pay for (L = 2048, D = 128, us an
+        // MCS alone and beside one 256-site member: 64 of them, p = 1 237 and 251, p = 0.7
+        // 270 and 334; 128, p = 0.7 450 and 663)
         if (any128 && any256) nw = 2u;
         nt = 64u * nw;
         cpt = max_cells / nt;

@@ -13,12 +13,12 @@
 //    sites of the round after it drawn and published (every lane publishes
 //    its own and reads its two neighbours').
 //
-// Four tiles (L = 1024, p = 0.8) 64.1 us a step against 54.5, 256 tiles 68.5
-// against 57; D = 128: four tiles 48 against 34, 1024 tiles 60 against 52.  A
-// round is then about 0.7 us: the waves' LDS and vector phases, 0.3 us each,
-// fall together between barriers.  With more tiles than compute units the
-// row-paired kernel's smaller workgroups win (1024 tiles of D = 256: 128 us
-// against 226; 4096 of D = 128: 128 against 138).
+// us a step, two cells per lane in the row-paired kernel against this, p = 0.7:
+// D = 256, one tile 60.8 and 51.2, 64 tiles 63.5 and 53.0; D = 128, four tiles 46.7
+// and 32.2, 256 tiles 48.6 and 33.6.  A round is then about 0.7 us: the waves'
+// LDS and vector phases, 0.3 us each, fall together between barriers.  With
+// more tiles than compute units the row-paired kernel's smaller workgroups
+// win (1024 tiles of D = 256: 128 us against 226; 4096 of D = 128: 125 against 129).
 #pragma once
 
 #include "db_rows.hpp"

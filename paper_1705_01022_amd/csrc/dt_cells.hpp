@@ -24,15 +24,17 @@
 //    sites' bits are one packed 16-bit shift, the acceptance masks a packed
 //    subtraction and sign.
 //
-// The step is bound by vector issue: 90 % VALU busy at p = 1 (95 % with
-// draws), where the row-paired LDS kernel it replaces was bound by LDS and
-// issue together (73 % and 69 %).  D = 256, L = 2^16, per launch: p = 1 0.863
-// -> 0.41 ms (28.6 -> 14.3 VALU instructions per wave-attempt), p = 0.95
-// 0.94 -> 0.68 ms; D = 128 p = 1 0.90 -> 0.47 ms, p = 1/2 0.96 -> 0.65 ms; 64
-// tiles (L = 4096) 31.1 -> 22.4 us.  Two waves per tile rather than one (which
-// needs no barrier and fewer instructions): a single wave holds 16 cells a
-// lane, 168 registers with spills, three waves per SIMD, 66-77 % VALU busy and
-// 0.51 ms (0.97 with draws).
+// The step is bound by vector issue (the counters read 100 % busy at p = 1,
+// 89 % with draws, where two waves' 132 registers leave three waves a SIMD), where
+// the row-paired LDS kernel it replaces was bound by LDS and issue together
+// (73 % and 69 %).  D = 256, L = 2^16, a launch among many, rows against this: p = 1
+// 0.845 and 0.394 ms (28.6 and 14.6 VALU instructions per wave-attempt), p = 0.95
+// 0.924 and 0.777 (25.0 instructions); D = 128 p = 1 0.89 and 0.44 ms, p = 1/2 0.95
+// and 0.63; 64 tiles (L = 4096), p = 1 31.3 and 23.2 us.  With few tiles and draws
+// the row-paired kernel is faster and taken (dt_rows_few).  Two waves per tile
+// rather than one (which needs no barrier and fewer instructions): a single
+// wave holds 16 cells a lane, 168 registers with spills, three waves per
+// SIMD, and took 0.51 ms a launch where two took 0.435 (0.97 with draws).
 #pragma once
 
 #include "kernels.hpp"

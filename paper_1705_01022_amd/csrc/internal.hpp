@@ -303,11 +303,14 @@ inline bool dt_rows_few(uint32_t dom, uint32_t threads, bool draws, uint64_t nti
     return draws || threads >= ncell;
 }
 
-// Waves per tile of the DT step in registers: one for 128-site domains (two leave a lane one
-// pair of cells: L = 2^16 at p = 1 0.79 ms a launch against 0.47); for 256-site
-// domains two, or four when a step has fewer tiles than four per compute unit
-// (p = 1, two against four: 1024 tiles 48 against 51 us, 256 tiles 34 against
-// 29, 64 tiles 33 against 28), or what the workgroup size asks for.
+// Waves per tile of the DT step in registers: one for 128-site domains (two leave
+// a lane one pair of cells: p = 1, us an MCS with one and with two, one tile 72 and
+// 80, 1024 tiles 90 and 105); for 256-site domains two, or four when a step has fewer
+// tiles than four per compute unit, or what the workgroup size asks for.  us a
+// launch with two waves and with four, p = 1: one tile 27 and 22, 64 tiles 28 and 23,
+// 256 30 and 25, 1024 43 and 42, 4096 116 and 110, 16384 393 and 397.  The rule does
+// not look at how the rounds decide; with draws (two waves hold 132 registers,
+// three waves a SIMD) p = 0.7: 1024 tiles 73 and 70, 4096 222 and 197, 16384 773 and 707.
 inline uint32_t dt_cells_waves(uint32_t dom, uint32_t threads, uint64_t ntiles, uint32_t cus)
 {
     if (dom == 128u) return 1u;

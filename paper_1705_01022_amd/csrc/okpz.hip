@@ -565,7 +565,7 @@ int okpz_run(okpz_lattice *lat, uint64_t n_mcs, double p, double q)
     if (n_mcs > kMcsLimit || lat->mcs + n_mcs > kMcsLimit) return OKPZ_EOVERFLOW;
     const LaneShape ls = lane_shape(lat->prm, p, q);
     StepArgs a = base_args(lat, ls, p, q);
-    // small lattices run whole MCS in one launch (44 against 93 us an MCS for
+    // small lattices run whole MCS in one launch (44 against 90 us an MCS for
     // L = 64, DT), unless a workgroup size is asked for or every step's launch
     // is to be timed; 4096 MCS bound a launch to about 0.4 s
     if (lat->prm.L <= kSmallLatticeL && lat->prm.cell_x == 8u && lat->prm.cell_y == 8u && !a.dev_db &&

@@ -2,11 +2,11 @@
 // device level) in one wave: the lattice lies in LDS as rows of bits, a lane
 // holds one cell of one of the step's tiles (L^2 / 256 <= 64 of them, and 64
 // is what bounds L).  Launched step by step, an MCS of L = 64 is four launches
-// of a few lanes each (p = 1: DT 93, DB 159 us an MCS); here any number of MCS
+// of a few lanes each (p = 1: DT 90, DB 159 us an MCS); here any number of MCS
 // is one launch, a round has no barrier, the tiles' block draws are worked out
 // by all lanes at the start of a step, and the draws of the next round while
-// this round's slope words are on their way: DT 44, DB 66 us (p = .6, q = .4:
-// 104 -> 58 and 175 -> 83; L = 128, D = 64: DT 122 -> 44, DB 188 -> 70).  What
+// this round's slope words are on their way: DT 44, DB 64 us (p = .6, q = .4:
+// 101 -> 60 and 175 -> 83; L = 128, D = 64: DT 116 -> 43, DB 187 -> 69).  What
 // bounds it is one wave's serial chain, 0.17 us a round of about 70
 // instructions and one LDS round trip.
 #pragma once

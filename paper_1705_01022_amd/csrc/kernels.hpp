@@ -623,12 +623,14 @@ __host__ __device__ inline uint32_t step_lds_words(uint32_t NR, uint32_t P, uint
 // 64 blocks where 8 x 8-site cells use eight, so single lattices, whose scalar
 // unit has room, lose by it (L = 1024, D = 16, p = 1: 97.6 us an MCS against
 // 102.5; L = 8192, D = 128, 16 x 16 cells, draws: 497 against 519), and so do
-// the batch's sweeps with four cells per lane or more (1600 tiles of D = 512:
-// 5.36 ms an MCS against 5.41, with 16 x 16 cells 5.57 against 5.68).  The
-// batch spills scalar registers, fewer of them so; with one cell per lane and draws it gains:
-// 64 realisations of L = 1024, D = 64, 16 x 16 cells 1036 us by the scalar unit,
-// 994 by the lanes; D = 128, 16 x 16 cells 653 and 643; D = 64, 8 x 8 cells,
-// L = 512 218.4 and 215.6; without draws D = 64 DTr 209.5 and 210.5.
+// the batch's sweeps with four cells per lane or more (1600 tiles of D = 512, draws:
+// 5.29 ms an MCS against 5.41, with 16 x 16 cells 5.49 against 5.68), those with
+// one and no draws (D = 64, p = 1, DTr 208 against 215 us) and those of 16 rounds (D = 32,
+// 4 x 4 cells, draws 445 against 457).  The batch spills scalar registers, fewer of them
+// so; it takes the lanes with one cell per lane and draws and with two cells, from
+// 64 rounds on (us an MCS by the scalar unit and by the lanes: 64 realisations of L = 1024,
+// D = 64, 16 x 16 cells 1036 and 987; D = 256, 16 x 16 cells, draws 865 and 852; 256 x 128 sites,
+// 8 x 8 cells, DTr, p = 1 382 and 365).
 template <int SCHEME, bool ACCEPT, int CPT, bool FULL, bool LANES = false>
 __device__ __forceinline__ void sweep_tile(const StepArgs &A, uint32_t *smem, uint32_t tile)
 {

@@ -409,7 +409,8 @@ int okpz_batch_size(const okpz_batch *batch, uint32_t *nslots);
  * Launch shape (physical mapping only; results do not depend on it):
  * threads per workgroup (64, 128, 256, 512, or 0: enough lanes for the
  * largest domain's cells, at most 256, or 512 when the launch has fewer
- * tiles per step than four per compute unit, and at most half the cells of
+ * tiles per step than four per compute unit, eight for DB on domains of 2^17
+ * sites and more or of 2048 cells, and at most half the cells of
  * a domain of 256 cells or more; the kernels made for a shape set their own
  * as for okpz_set_threads; DB on their domains takes two cells per thread in
  * place of four with fewer tiles than four per compute unit, and always at

@@ -7,6 +7,12 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+def compute_units():
+    import torch
+
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
 def run(okpz, orc, n, L, D, threads, p, q, check):
     print("db batch: %d x L=%d D=%d threads=%d p=%r" % (n, L, D, threads, p), flush=True)
     b = okpz.Batch()
@@ -33,7 +39,7 @@ def test_two_cells_with_few_tiles(okpz, orc, p, q):
 
 @pytest.mark.parametrize("p,q", [(1.0, 0.0), (0.7, 0.3)])
 def test_four_cells_with_many_tiles(okpz, orc, p, q):
-    cus = __import__("torch").cuda.get_device_properties(0).multi_processor_count
+    cus = compute_units()
     n = 4 * cus // 16 + 1  # L = 2048, D = 256: 16 tiles a step each
     assert run(okpz, orc, n, 2048, 256, 256, p, q, (0, n - 1)) == (256, 4)
     assert run(okpz, orc, n // 4 + 1, 2048, 128, 64, p, q, (0,)) == (128, 2)
@@ -74,7 +80,7 @@ def default_shape(okpz, n, L, Dx, Dy, C):
 
 
 def test_default_lanes_with_many_tiles(okpz):
-    cus = __import__("torch").cuda.get_device_properties(0).multi_processor_count
+    cus = compute_units()
     tiles = lambda per: 4 * cus // per + 1  # lattices for a few more than four tiles per compute unit
     assert default_shape(okpz, tiles(16), 2048, 256, 256, 8) == (256, 4)
     assert default_shape(okpz, tiles(16), 2048, 512, 128, 8) == (256, 4)
